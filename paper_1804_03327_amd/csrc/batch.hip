@@ -444,6 +444,169 @@ __device__ __forceinline__ void mb_pull_body(const BatchArgs& a, const LevelStat
   }
 }
 
+// Whether the pull of a level reads the frontier through a filter (mb_pull_sparse): right after
+// a push that listed its winners, while the list is short. Lists past kMbSparseNf entries let
+// more than one entry in eight through a filter of kMbFilterBits bits, and reading the list in
+// every block costs more than it saves.
+constexpr int kMbSparseNf = 8192;
+constexpr int kMbFilterBits = 16;
+constexpr int kMbSparseU = 4;                   // entries a lane reads at once
+constexpr int kMbSparseWin = 64 * kMbSparseU;   // entries of a wave's window
+__device__ __forceinline__ bool mb_sparse_level(const LevelState& st) {
+  return st.local == 1 && st.list_valid && st.nf <= kMbSparseNf;
+}
+
+struct MbSparseShared {
+  uint32_t filter[1 << (kMbFilterBits - 5)];
+  uint64_t acc[kMbTileV];
+  int32_t off[kMbTileV + 1];
+  uint32_t nzf[kMbTileWords];
+  int32_t pass_j[kThreads / 64][kMbSparseWin];   // per wave: the in-neighbours the filter let through
+  uint8_t pass_e[kThreads / 64][kMbSparseWin];   // and their places in the window
+};
+
+// Fills the block's filter: bit (j mod 2^kMbFilterBits) for every frontier vertex j.
+__device__ __forceinline__ void mb_filter_build(const BatchArgs& a, const LevelState& st, MbSparseShared& sh) {
+  for (int i = threadIdx.x; i < (1 << (kMbFilterBits - 5)); i += kThreads) sh.filter[i] = 0;
+  __syncthreads();
+  const int32_t* Q = a.Q[st.level % 2];
+  constexpr uint32_t kMask = (1u << kMbFilterBits) - 1u;
+#pragma unroll 4
+  for (int32_t i = threadIdx.x; i < st.nf; i += kThreads) {
+    const uint32_t j = uint32_t(Q[i]) & kMask;
+    atomicOr(&sh.filter[j >> 5], 1u << (j & 31));
+  }
+  __syncthreads();
+}
+
+// The pull of one tile when few vertices carry frontier bits: hardly any row is completed by
+// them, so nearly every row is read to its end and an early exit saves nothing. A random 8-byte
+// frontier word per in-neighbour is what that costs row by row (64 sources on RMAT-20, 31.4 M
+// in-neighbours, frontiers of 1275 and 2509 vertices: 0.70 and 0.80 ms for that level), and
+// nearly all of those words are zero. So the tile's entries are read as
+// one contiguous run, each wave a window of it at a time with the next window's loads behind it,
+// and looked up in the filter in LDS; the entries it lets through are packed into a list, and the
+// wave takes them 64 at a time (0.12 and 0.15 ms): find the row (a search over the tile's offsets), read the frontier
+// word, OR it into the row's accumulator. Without the packing almost every wave ran the search
+// and the word's load for a few of its lanes (0.17 and 0.22 ms).
+// When less than half of the tile's entries belong to rows that still miss a source, a wave takes
+// each of those rows instead, 64 entries at a time.
+__device__ __forceinline__ void mb_pull_sparse(const BatchArgs& a, const LevelState& st, int32_t s, int32_t tile,
+                                               MbSparseShared& sh) {
+  static_assert(kMbTileV == kThreads, "one row per thread");
+  const int tid = threadIdx.x;
+  const int32_t L = st.level;
+  const int32_t w0 = tile * kMbTileWords;
+  const int32_t v = w0 * 32 + tid;
+  const uint64_t* vin = a.vis[st.vis_idx];
+  uint64_t* vout = a.vis[st.vis_idx ^ 1];
+  uint64_t* Fn = mb_frontier(a, L + 1);
+  const uint64_t* Fc = mb_frontier(a, L);
+  const uint64_t active = st.active;
+  const bool in = v < a.V;
+  const uint64_t m = in ? (vin[v] | Fc[v]) : 0ull;
+  const uint64_t need = in ? (~m & active) : 0ull;
+  const int32_t vc = min(v, a.V);  // offsets past the last row: its end
+  const int32_t beg = a.colptr[vc], end = in ? a.colptr[v + 1] : beg;
+  if (tid < kMbTileWords) sh.nzf[tid] = 0;
+  sh.acc[tid] = 0ull;
+  sh.off[tid] = beg;
+  if (tid == kThreads - 1) sh.off[kMbTileV] = end;
+  uint32_t wanted;
+  block_excl_scan(need ? uint32_t(end - beg) : 0u, &wanted);  // (barriers: off and acc are written)
+  const int32_t base = sh.off[0];
+  const uint32_t total = uint32_t(sh.off[kMbTileV] - base);
+  constexpr uint32_t kMask = (1u << kMbFilterBits) - 1u;
+  constexpr int kU = kMbSparseU;
+  static_assert(kMbSparseWin <= 256, "window places in 8 bits");
+  const int wv = tid >> 6, ln = lane();
+  const int32_t* ind = a.rowind + base;
+  auto filtered = [&](int32_t x) {
+    const uint32_t h = uint32_t(x) & kMask;
+    return ((sh.filter[h >> 5] >> (h & 31)) & 1u) != 0;
+  };
+  auto load = [&](uint32_t e0, int32_t j[kU]) {
+#pragma unroll
+    for (int q = 0; q < kU; ++q) {
+      const uint32_t e = e0 + uint32_t(q * 64 + ln);
+      j[q] = e < total ? ind[e] : -1;
+    }
+  };
+  if (wanted >= total - wanted) {
+    constexpr uint32_t kStep = uint32_t(kThreads / 64 * kMbSparseWin);
+    int32_t j[kU];
+    uint32_t e0 = uint32_t(wv * kMbSparseWin);
+    load(e0, j);
+    for (; e0 < total; e0 += kStep) {
+      int32_t jn[kU];
+      load(e0 + kStep, jn);
+      int n = 0;
+#pragma unroll
+      for (int q = 0; q < kU; ++q) {
+        const bool pass = j[q] >= 0 && filtered(j[q]);
+        const uint64_t bal = __ballot(pass);
+        if (pass) {
+          const int p = n + __popcll(bal & lanemask_lt());
+          sh.pass_j[wv][p] = j[q];
+          sh.pass_e[wv][p] = uint8_t(q * 64 + ln);
+        }
+        n += __popcll(bal);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the list is this wave's own
+      for (int i = ln; i < n; i += 64) {
+        const uint64_t x = Fc[sh.pass_j[wv][i]] & active;
+        const int32_t r = thread_search(sh.off, 0, kMbTileV, uint32_t(base) + e0 + sh.pass_e[wv][i]);
+        if (x) atomicOr((unsigned long long*)&sh.acc[r], (unsigned long long)x);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int q = 0; q < kU; ++q) j[q] = jn[q];
+    }
+  } else {
+    uint64_t rows = __ballot(need != 0 && end > beg);  // this wave's 64 rows that miss a source
+    while (rows) {
+      const int r = __ffsll((unsigned long long)rows) - 1;
+      rows &= rows - 1;
+      const int32_t b = __builtin_amdgcn_readlane(beg, r), e = __builtin_amdgcn_readlane(end, r);
+      uint64_t x = 0;
+      for (uint32_t p = uint32_t(b); p < uint32_t(e); p += 64) {
+        const int32_t jj = p + ln < uint32_t(e) ? a.rowind[p + ln] : -1;
+        if (jj >= 0 && filtered(jj)) x |= Fc[jj] & active;
+      }
+      if (x) atomicOr((unsigned long long*)&sh.acc[wv * 64 + r], (unsigned long long)x);
+    }
+  }
+  __syncthreads();
+  const uint64_t found = sh.acc[tid] & need;
+  unsigned long long v4[4] = {0, 0, 0, 0};
+  unsigned long long insub = 0;
+  if (in) {
+    vout[v] = m | found;
+    Fn[v] = found;
+  }
+  if (found) {
+    atomicOr(&sh.nzf[tid >> 5], 1u << (tid & 31));
+    stamp_levels(a.lvl, a.k, v, found, L);
+    v4[0] = 1;
+    v4[1] = uint64_t(__popcll(found));
+    if (a.edge_rule) {
+      v4[3] = uint64_t(a.rowptr[v + 1] - a.rowptr[v]);
+      if (((m | found) & a.active) == a.active) insub = uint64_t(end - beg);
+    }
+  }
+  __syncthreads();
+  if (tid < kMbTileWords && w0 + tid < a.nwords) a.nzF[(L + 1) % 2][w0 + tid] = sh.nzf[tid];
+  block_sum4(v4);
+  unsigned long long i4[4] = {insub, 0, 0, 0};
+  block_sum4(i4);
+  const uint64_t fbits = block_or64(found);
+  if (tid == 0) {
+    stripe_add(&a.ctrl->slot[s % kSlots], v4[0], v4[1], wanted >= total - wanted ? total : wanted, v4[3],
+               i4[0]);
+    stripe_or(&a.ctrl->slot[s % kSlots], fbits);
+  }
+}
+
 // ---------------------------------------------------------- step loop
 // One launch per step. Every block derives step s's state from the state step
 // s-1 published and the counters it left (one round trip): the expansion that
@@ -575,6 +738,7 @@ __device__ __forceinline__ void mb_scan_step(const BatchArgs& a, const LevelStat
 union MbShared {
   MbExpandShared e;
   MbPullShared p;
+  MbSparseShared f;
 };
 
 // The work of step s (state st, prev: the state before it) over the launch's grid.
@@ -586,6 +750,15 @@ __device__ __forceinline__ void mb_step_body(const BatchArgs& a, const LevelStat
     mb_expand_body(a, st, s, sh.e);
   } else {
     const int32_t ntiles = (a.nwords + kMbTileWords - 1) / kMbTileWords;
+    if (mb_sparse_level(st)) {
+      if (int32_t(blockIdx.x) >= ntiles) return;
+      mb_filter_build(a, st, sh.f);
+      for (int32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        mb_pull_sparse(a, st, s, t, sh.f);
+        __syncthreads();  // LDS of this tile is no longer read
+      }
+      return;
+    }
     for (int32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
       __syncthreads();  // LDS of the previous tile is no longer read
       mb_pull_body(a, st, s, t, sh.p);

@@ -355,3 +355,31 @@ def test_batch_last_level_pull_after_push(graphs, name):
         d, st = _run(g, srcs, dobfs.make_options("full", forced_dirs=sc))
         _check(hg, srcs, d, st, tag)
         assert [x["dir"] for x in dobfs.stats_levels(st)] == sc, tag
+
+
+@pytest.mark.parametrize("leaves", [1, 254, 255, 256, 2047, 8191, 8192, 8193])
+def test_batch_pull_after_short_list(leaves):
+    """A pull right after a push that listed its winners reads the frontier through a filter while
+    the list has at most 8192 entries: a hub joined to `leaves` vertices, every leaf with a tail
+    of two more and some leaves joined to each other, so that a tile's entries belong to rows that
+    still miss a source (the filtered form), or mostly do not, and rows of many and of no entries
+    meet in one tile; V is ragged."""
+    rng = np.random.default_rng(leaves)
+    hub, first = 0, 1
+    leaf = np.arange(first, first + leaves)
+    mid = leaf + leaves
+    end = mid + leaves
+    V = 1 + 3 * leaves + 5  # the last five vertices are isolated
+    pick = rng.integers(0, leaves, (2, 4 * leaves))
+    src = np.concatenate([np.full(leaves, hub), leaf, mid, leaf[pick[0]]])
+    dst = np.concatenate([leaf, mid, end, end[pick[1]]])
+    hg = gen.from_edges(V, src, dst, directed=False, name="hub%d" % leaves)
+    g = upload(hg)
+    sets = [[hub], [hub, int(mid[-1]), int(end[0])], [hub] * 3 + [V - 1, int(leaf[0])]]
+    for srcs in sets:
+        for sc in ([PUSH, PULL], [PUSH, PULL, PUSH, PULL, PULL], [PUSH, PUSH, PULL, PUSH, PULL]):
+            for heur in (dobfs.HEUR_RATIO, dobfs.HEUR_EDGES):
+                tag = "hub%d k=%d forced %s heur=%d" % (leaves, len(srcs), sc, heur)
+                d, st = _run(g, srcs, dobfs.make_options("full", heur, 0.01, 0.01, forced_dirs=sc))
+                _check(hg, srcs, d, st, tag)
+    dobfs.graph_destroy(g)
