@@ -241,10 +241,14 @@ struct ReportSink {
 
 hipError_t fetch_report(const ReportSink& r, uint32_t seq, hipStream_t s) {
   if (r.dev == r.host) return wait_report(r.host, seq, s);
-  hipError_t e = hipMemcpyAsync(r.host, r.dev, sizeof(HostReport), hipMemcpyDeviceToHost, s);
+  hipError_t e = hipMemcpyAsync(r.host, r.dev, offsetof(HostReport, rec), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return e;
-  return r.host->seq == seq ? hipSuccess : hipErrorUnknown;
+  if (r.host->seq != seq) return hipErrorUnknown;
+  if (r.host->nrec <= 0) return hipSuccess;
+  e = hipMemcpyAsync(r.host->rec, r.dev->rec, sizeof(LevelRecord) * size_t(r.host->nrec), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  return e;
 }
 
 // Per-thread, per-device events for the level loop's timers: the start and
@@ -488,6 +492,7 @@ BfsArgs bfs_args(dobfs_graph g, uint8_t* ws, const Layout& L, const dobfs_option
   a.edge_rule = opt.heuristic == DOBFS_HEUR_EDGES ? 1 : 0;
   a.local_push = a.need_F ? 0 : 1;  // (the frontier bitmap a push writes is cleared by its scan step)
   a.low_degree = g->max_outdeg <= uint32_t(kLocalDeg) ? 1 : 0;
+  a.max_outdeg = g->max_outdeg;
   a.sched = default_sched();
   if (opt.pull_mid) a.sched.pull_mid = opt.pull_mid;
   if (opt.bitmap_rows) a.sched.bitmap_rows = opt.bitmap_rows;
@@ -550,14 +555,26 @@ uint32_t env_u32(const char* name, uint32_t dflt) {
 // persistent(): the persistent form of a batch (rp as for step()); grid(): the full grid of a
 // step launch; next_grid(): the blocks for the next batch's launches from the report of the
 // batch before (0: the full grid); capacity(): blocks of the persistent kernel that fit at once.
+constexpr int32_t kBurstLevels = 4096;  // levels the bursts of one batch run at most (about 10 ms of a deep graph)
 struct SingleSteps {
   const BfsArgs& a;
+  bool burst;  // not for timed calls (a level per launch) and the modes whose pushes need the scan
   static constexpr bool self_report = true;
   int64_t grid() const { return main_blocks(a.nwords); }
   int64_t next_grid(const HostReport&, int32_t) const { return 0; }
   static int32_t capacity(const PersistentDevice& d) { return d.capacity; }
-  hipError_t step(hipStream_t s, int32_t k, int64_t, hipEvent_t t0, hipEvent_t t1, const StepReportArgs* rp) const {
-    return launch_step(s, a, k, t0, t1, rp);
+  hipError_t step(hipStream_t s, int32_t k, int64_t, bool narrow, hipEvent_t t0, hipEvent_t t1,
+                  const StepReportArgs& rp) const {
+    return launch_step(s, a, k, t0, t1, rp, burst && (narrow || k == 0));
+  }
+  // Whether launches are given the form that runs several narrow levels at once: the first launch
+  // always (a traversal starts at one vertex), the rest of the first batch on graphs without hubs
+  // (meshes, roads and trees, whose frontiers stay narrow; where there are hubs the second or third
+  // level is wide already), and later batches as the batch before ended.
+  bool narrow_first() const { return a.low_degree != 0; }
+  bool narrow_next(const HostReport& r) const {
+    const LevelState& st = r.end;
+    return st.dir == DOBFS_DIR_PUSH && uint32_t(st.nf) <= kBurstNf * kBurstBlocks;
   }
   hipError_t before_report(hipStream_t, int32_t) const { return hipSuccess; }
   hipError_t persistent(hipStream_t s, int32_t s_first, int32_t n, int32_t blocks, uint32_t spin_limit,
@@ -595,8 +612,10 @@ struct BatchSteps {
     return g < grid() ? g : 0;
   }
   static int32_t capacity(const PersistentDevice& d) { return d.capacity_mb; }
-  hipError_t step(hipStream_t s, int32_t k, int64_t blocks, hipEvent_t t0, hipEvent_t t1,
-                  const StepReportArgs*) const {
+  bool narrow_first() const { return false; }
+  bool narrow_next(const HostReport&) const { return false; }
+  hipError_t step(hipStream_t s, int32_t k, int64_t blocks, bool, hipEvent_t t0, hipEvent_t t1,
+                  const StepReportArgs&) const {
     return launch_mb_step(s, a, k, blocks, t0, t1);
   }
   // the depth rows: a transpose that exits at once unless the state the batch's last step
@@ -639,31 +658,37 @@ dobfs_status run_steps(std::atomic<int32_t>& last_steps, hipStream_t s, bool tim
     return fail(DOBFS_ERR_INVALID_ARG, "persistent grid of %d blocks (1 .. %d fit)", blocks, cap);
   if (pd) batch = next_batch = kMaxBatch;  // a launch ends with the traversal: no steps past the end
   int64_t grid = 0;  // blocks of the step launches (0: the full grid)
+  bool narrow = S.narrow_first();
   while (true) {
     if (s0 + batch > max_steps) batch = int32_t(max_steps - s0);
     const uint32_t seq = next_report_seq();
     // untimed, the batch's last step writes the report; timed, a report kernel follows the
     // steps so that every step's end event has completed when the host reads it
-    const StepReportArgs rp{sink.dev, seq, int32_t(s0), rec_first};
+    // the records are read only for the stats; without them a burst may run any number of levels
+    const int32_t rec_from = stats ? rec_first : INT32_MAX;
+    const int32_t level_end = rec_first + (stats ? kMaxRec - batch : kBurstLevels);
+    const StepReportArgs rp{sink.dev, seq, int32_t(s0), rec_from, level_end};
+    const StepReportArgs no_report{nullptr, 0u, 0, 0, level_end};
     const bool self = Steps::self_report && !timing;
     if (pd) {
       std::lock_guard<std::mutex> lk(pd->mu);
       HIPCK(S.persistent(s, int32_t(s0), batch, blocks, spin_limit, timing,
-                         self ? rp : StepReportArgs{nullptr, 0u, 0, 0}, E(ev_m0(0)), E(ev_m1(0))));
+                         self ? rp : no_report, E(ev_m0(0)), E(ev_m1(0))));
       HIPCK(S.before_report(s, int32_t(s0 + batch - 1)));
-      if (!self) HIPCK(launch_step_report(s, ctrl, int32_t(s0), batch, rec_first, sink.dev, seq));
+      if (!self) HIPCK(launch_step_report(s, ctrl, int32_t(s0), batch, rec_from, sink.dev, seq));
       HIPCK(fetch_report(sink, seq, s));
     } else {
       for (int32_t k = 0; k < batch; ++k)
-        HIPCK(S.step(s, int32_t(s0 + k), grid, E(ev_m0(k)), E(ev_m1(k)), (self && k == batch - 1) ? &rp : nullptr));
+        HIPCK(S.step(s, int32_t(s0 + k), grid, narrow, E(ev_m0(k)), E(ev_m1(k)),
+                     (self && k == batch - 1) ? rp : no_report));
       HIPCK(S.before_report(s, int32_t(s0 + batch - 1)));
-      if (!self) HIPCK(launch_step_report(s, ctrl, int32_t(s0), batch, rec_first, sink.dev, seq));
+      if (!self) HIPCK(launch_step_report(s, ctrl, int32_t(s0), batch, rec_from, sink.dev, seq));
       HIPCK(fetch_report(sink, seq, s));
     }
     if (rep->error) {
       (void)hipStreamSynchronize(s);
-      return fail(DOBFS_ERR_INTERNAL, "a grid barrier wait of the persistent level loop gave up "
-                                      "(spin limit %u polls)", spin_limit);
+      return fail(DOBFS_ERR_INTERNAL, "a wait between the blocks of a level loop gave up (persistent loop: a grid "
+                                      "barrier, spin limit %u polls)", spin_limit);
     }
     res->n_main += pd ? 1 : batch;
     if (pd && timing) res->ms_main_all += elapsed(ev[ev_m0(0)], ev[ev_m1(0)]);
@@ -698,8 +723,9 @@ dobfs_status run_steps(std::atomic<int32_t>& last_steps, hipStream_t s, bool tim
         ls.m_f = r.m_f;
       }
     }
-    rec_first += rep->nrec;
+    rec_first = rep->end.done ? rep->end.levels : rep->end.level;
     grid = S.next_grid(*rep, batch);
+    narrow = S.narrow_next(*rep);
     const LevelState& end = rep->end;
     if (end.done) {
       res->levels = end.levels;
@@ -880,7 +906,7 @@ dobfs_status bfs_steps(dobfs_graph g, int32_t source, const dobfs_options& opt, 
     pd = persistent_device(g->device);
     if (!pd) return fail(DOBFS_ERR_UNSUPPORTED, "the persistent level loop is not available on device %d", g->device);
   }
-  dobfs_status st = run_steps(g->last_steps, s, timing, ev, SingleSteps{a}, a.ctrl, max_steps,
+  dobfs_status st = run_steps(g->last_steps, s, timing, ev, SingleSteps{a, a.local_push && !timing}, a.ctrl, max_steps,
                               INT64_MAX, DOBFS_ERR_INTERNAL, sink, pd, stats, &res);
   if (st != DOBFS_OK) return st;
   if (stats) {

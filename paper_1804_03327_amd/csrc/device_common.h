@@ -421,6 +421,8 @@ __device__ __forceinline__ int32_t thread_search(const int32_t* S, int32_t lo, i
 // the in-degrees of the rows they find.
 __device__ __forceinline__ bool recounts_mu(const BfsArgs& a) { return a.edge_rule != 0; }
 __device__ __forceinline__ bool recounts_mu(const BatchArgs&) { return false; }
+__device__ __forceinline__ uint32_t level_max_outdeg(const BfsArgs& a) { return a.max_outdeg; }
+__device__ __forceinline__ uint32_t level_max_outdeg(const BatchArgs&) { return 0xffffffffu; }
 // The multi-source traversal also needs the (vertex, source) pair counts and the source bits.
 __host__ __device__ constexpr bool is_batch(const BfsArgs&) { return false; }
 __host__ __device__ constexpr bool is_batch(const BatchArgs&) { return true; }
@@ -536,6 +538,11 @@ __device__ LevelState next_state(const Args& a, int32_t L, int32_t forced, const
           const int64_t mf_b = tracked ? int64_t(t.mnew) : INT64_MAX;
           const int64_t md_b = tracked ? int64_t(__builtin_amdgcn_readfirstlane(wave_max32(x.maxdeg))) : int64_t(kLocalDeg);
           const int64_t G = main_blocks(a.nwords);
+          if (!batch) {  // what a burst needs to know of the level (sizes; bounds when untracked)
+            const uint64_t mf_n = tracked ? t.mnew : uint64_t(n_new) * level_max_outdeg(a);
+            const uint64_t md_n = tracked ? uint64_t(md_b) : uint64_t(level_max_outdeg(a));
+            st.active = ((mf_n < 0xffffffffull ? mf_n : 0xffffffffull) << 32) | md_n;
+          }
           if (a.low_degree || local_fits(n_new, mf_b, md_b, G, a.sched.local_unit, a.sched.local_chunks)) {
             st.local = 1;
             st.share = local_share(n_new, mf_b, md_b, G, a.sched.local_unit);
@@ -630,6 +637,8 @@ __device__ __forceinline__ void publish_step(Ctrl* c, int32_t s, const LevelStat
     if (new_level) c->rec[(st.level - 1) % kRing] = step_record(c, s, prev, tot);
     c->qcount[(s + 2) % kSlots] = 0;
     c->ticket[(s + 1) % 2] = 0;
+    c->burst.joined[(s + 2) % kSlots][0] = 0;
+    c->burst.members[(s + 2) % kSlots][0] = 0;
   }
   for (int k = threadIdx.x; k < kStripes; k += blockDim.x) zero_stripe(c->slot[(s + 2) % kSlots].s[k]);
 }

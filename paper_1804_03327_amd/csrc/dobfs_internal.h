@@ -50,7 +50,9 @@ struct alignas(64) LevelState {
   int32_t share;       // local 1: blocks that share one unit's edge chunks (local_share)
   int32_t phase;       // step loops: kPhaseWhole, kPhaseScan or kPhaseExpand
   int64_t m_u;         // edge-count rule: in-edges of still-unvisited vertices
-  uint64_t active;     // multi-source: sources whose frontier entering the level is non-empty
+  uint64_t active;     // multi-source: sources whose frontier entering the level is non-empty;
+                       // single source: of a push with local 1, its out-edges << 32 | largest
+                       // out-degree (upper bounds), else 0
   uint64_t t0;         // single source, persistent loop: device clock when the step started
 };
 static_assert(sizeof(LevelState) == 64, "one state per 64-byte line");
@@ -87,6 +89,22 @@ struct GridBar {
   alignas(128) unsigned long long t_end;  // timing: latest block end of the last launch (device clock)
 };
 
+// A burst: consecutive narrow levels run by a few blocks of one step launch (burst_run). Blocks
+// join in slot s % kSlots of step s; the leader closes the slot and publishes how many joined and
+// where the append counter `head` stands (the counter only grows within a traversal). Members
+// leave their totals in rec, every word with a tag that grows through the traversal in its upper
+// half, and wait for everybody's: the exchange of the totals is the barrier.
+constexpr int kBurstBlocks = 32;      // members at most: about one per CU of an XCD
+constexpr int kBurstWords = 8;
+constexpr uint32_t kBurstNf = 128;    // most frontier vertices of a burst level, per member
+struct BurstCtl {
+  alignas(128) uint32_t joined[kSlots][32];          // a line per slot; kBurstClosed: too late
+  alignas(128) unsigned long long members[kSlots][16];  // members | head << 32; 0: not yet known
+  alignas(128) uint32_t head;
+  alignas(128) unsigned long long rec[2][kBurstBlocks][kBurstWords];
+};
+constexpr uint32_t kBurstClosed = 1u << 31;
+
 struct Ctrl {
   unsigned long long ticket[2];  // scan tile tickets, one counter per level (or step) parity
   uint32_t mf32;                 // m_f of the latest frontier scan (expand reads it)
@@ -102,6 +120,7 @@ struct Ctrl {
   int8_t forced[kRing];          // step loops: forced direction of levels 0 .. n_forced-1
   LevelSlot tail;                // after a traversal: out-degree sum of the reached vertices (edges)
   GridBar bar;                   // the persistent loops' grid barrier
+  BurstCtl burst;
 };
 static_assert(sizeof(Stripe) == 128, "stripe layout");
 static_assert(offsetof(Ctrl, slot) % 128 == 0, "slots start on a line");
@@ -303,6 +322,7 @@ struct BfsArgs {
   int32_t local_push;        // push levels of small out-degree may skip the global scan
   int32_t low_degree;        // every out-degree of the graph is <= kLocalDeg
   int32_t n_forced;          // levels whose direction Ctrl::forced fixes
+  uint32_t max_outdeg;       // largest out-degree of the graph
   Sched sched;
 };
 
@@ -419,14 +439,15 @@ hipError_t launch_reached_degree(hipStream_t s, const int32_t* ptr, const int32_
 // the records of its levels. Written into pinned host memory by one block,
 // `seq` last (system-scope release), so the host can spin on it.
 constexpr int kMaxBatch = 64;
+constexpr int kMaxRec = kRing - kMaxBatch;  // levels a batch may complete when their records are wanted
 struct HostReport {
   LevelState end;
-  LevelRecord rec[kMaxBatch];
   LevelState steps[kMaxBatch];  // the state each step of the batch published
   int32_t nrec;                 // records in rec (levels rec_first ..)
   int32_t error;                // persistent loop: 1 when a grid barrier wait gave up
   unsigned long long t_end;     // persistent loop, timed: device clock when its last block ended
   uint32_t seq;
+  LevelRecord rec[kMaxRec];
 };
 // single-source step loop (kernels.hip); a step given report arguments also
 // writes the report of the batch it ends (block 0, after publishing its state)
@@ -434,9 +455,10 @@ struct StepReportArgs {
   HostReport* host;  // nullptr: no report
   uint32_t seq;
   int32_t s_first, rec_first;
+  int32_t level_end;  // a burst stops before it has completed this level (records of the report)
 };
-hipError_t launch_step(hipStream_t s, const BfsArgs& a, int32_t step, hipEvent_t t0 = nullptr,
-                       hipEvent_t t1 = nullptr, const StepReportArgs* rp = nullptr);
+hipError_t launch_step(hipStream_t s, const BfsArgs& a, int32_t step, hipEvent_t t0, hipEvent_t t1,
+                       const StepReportArgs& rp, bool burst);
 hipError_t launch_step_report(hipStream_t s, const Ctrl* ctrl, int32_t s_first, int32_t n, int32_t rec_first,
                               HostReport* host, uint32_t seq);
 // The persistent form of the step loop: one launch runs steps s_first .. s_first + n - 1 with a

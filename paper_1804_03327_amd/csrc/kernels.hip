@@ -11,7 +11,8 @@
 // two when its push needs the global degree scan (scan step, expansion step).
 // Every block of a step decides the level itself on the device (the rule of
 // Section 6.3, from the counters the previous step left). The host enqueues
-// many steps ahead and reads the states back once per batch. k_steps runs the
+// many steps ahead and reads the states back once per batch. A step whose level is narrow may run
+// the narrow levels after it too (burst_run). k_steps runs the
 // same steps in one persistent launch; k_level_prep serves the sort-based
 // push of Table 2's first rows, whose host loop sizes the sort per level.
 //
@@ -701,7 +702,14 @@ __global__ __launch_bounds__(kThreads) void k_bfs_init(BfsArgs a, int32_t source
     for (int k = threadIdx.x; k < kSlots * kStripes; k += blockDim.x)
       zero_stripe(c->slot[k / kStripes].s[k % kStripes]);
     if (threadIdx.x < kBarGroups) c->bar.group[threadIdx.x].n = 0;
+    for (int k = threadIdx.x; k < 2 * kBurstBlocks * kBurstWords; k += blockDim.x)
+      (&c->burst.rec[0][0][0])[k] = 0;
+    if (threadIdx.x < kSlots) {
+      c->burst.joined[threadIdx.x][0] = 0;
+      c->burst.members[threadIdx.x][0] = 0;
+    }
     if (threadIdx.x == 0) {
+      c->burst.head = 0;
       c->bar.top.n = 0;
       c->bar.gen = 0;
       c->bar.abort = 0;
@@ -726,7 +734,7 @@ __global__ __launch_bounds__(kThreads) void k_bfs_init(BfsArgs a, int32_t source
       st.levels = 0;
       st.level = 0;
       st.m_u = a.nnz - c->src_indeg;
-      st.active = 0;
+      st.active = (uint64_t(c->src_outdeg) << 32) | uint64_t(c->src_outdeg);
       st.local = (a.local_push && dir0 == 0 &&
                   local_fits(1, c->src_outdeg, c->src_outdeg, main_blocks(a.nwords), a.sched.local_unit,
                              a.sched.local_chunks)) ? 1 : 0;
@@ -846,7 +854,7 @@ __device__ __forceinline__ void step_report(const Ctrl* c, const StepReportArgs&
   const int32_t n = n_steps > 0 ? n_steps : s - rp.s_first + 1;
   for (int k = threadIdx.x; k < n - 1; k += blockDim.x) host->steps[k] = c->ring[(rp.s_first + k) % kRing];
   const int32_t upto = st.done ? st.levels : st.level;  // records exist for levels < upto
-  const int32_t nrec = max(0, min(upto - rp.rec_first, kMaxBatch));
+  const int32_t nrec = max(0, min(upto - rp.rec_first, kMaxRec));
   for (int k = threadIdx.x; k < nrec; k += blockDim.x) {
     const int32_t l = rp.rec_first + k;
     host->rec[k] = (new_level && l == st.level - 1) ? step_record(c, s, prev, tot) : c->rec[l % kRing];
@@ -1006,19 +1014,481 @@ __device__ __forceinline__ void step_body(const BfsArgs& a, const LevelState& st
   }
 }
 
-template <bool EE>
+// ------------------------------------------------------------ bursts
+// A level of a few thousand frontier vertices or fewer does not fill the chip: as a step of its own
+// it is a launch, the state and the counters, and a chain of cold loads (every launch starts with
+// invalidated caches), 8 to 12 us on a 2048 x 2048 grid whatever the frontier's size. A step whose
+// level is that narrow therefore goes on with the levels after it, as long as they are pushes that
+// share out their own work (LevelState::local 1) and stay narrow: up to kBurstBlocks of its blocks,
+// chosen so that they sit on one XCD and share its L2, each expand a part of the frontier and
+// exchange their totals in place of a kernel boundary. The other blocks of the launch leave at once.
+//
+// A member keeps the vertices it finds in LDS and expands them itself at the next level, with their
+// row extents, which it loads beside the claims. While it waits for the others it already loads
+// the next level's neighbours and their visited words; only the claims have to wait. The frontier
+// goes through the list in memory when one member's part outgrows the others', and at the end.
+//
+// Who takes part is settled at run time: the candidates join, the leader (block 0) waits for them a
+// few microseconds at most and closes the list, so every wait in a burst is for a block that is
+// running, whatever else occupies the device. Nothing but speed depends on where the members run:
+// all they pass to each other (list, claims, totals) is written and read by agent-scope atomics,
+// and a member publishes its totals only after what the others may read has completed. The visited
+// word an edge looks at before its claim may be stale; a stale word costs a claim that fails.
+//
+// Measured on 2048 x 2048 grids (2700 levels, frontiers up to 2758): 34.5 -> 13.6 ms per search
+// (12.5 -> 5.0 us per level); a tree of 750 000 vertices 505 -> 432 us. A burst level is bound by
+// its chain: neighbours, then visited words and row extents (0.9 us each when they miss the L2),
+// claims, totals. The limits are one round of a member's threads: a wider level would take it two,
+// and the whole chip runs levels of some ten thousand edges as fast.
+constexpr uint32_t kBurstEdges = 1024;       // most out-edges of a burst level, per member
+constexpr uint32_t kBurstDeg = 1024;         // largest out-degree (a row is one member's)
+constexpr int kBurstCap = 512;               // frontier vertices a member keeps in LDS
+constexpr uint32_t kBurstJoinPolls = 16;     // the leader's wait for the candidates (about 4 us)
+constexpr uint32_t kBurstSpin = 1u << 22;    // bound of every other wait (polls)
+constexpr int kBurstMapDeg = 2 * kExpandEPT; // rows of up to this many entries: two threads a vertex
+static_assert(kBurstBlocks * kBurstWords == kThreads, "a thread per exchanged word");
+
+struct BurstList {
+  int32_t v[kBurstCap], beg[kBurstCap], deg[kBurstCap];  // vertex, row start, out-degree
+};
+struct BurstShared {
+  BurstList list[2];                      // this member's part of the frontier, by level parity
+  int32_t off[kThreads + 1];              // degree prefix of up to kThreads of its vertices
+  uint32_t nbuf[2];                       // vertices found (kept in list or past it in memory)
+  uint32_t red[2][kBurstWords];           // this block's totals
+  alignas(16) uint32_t tot[kBurstWords][kThreads / 64];
+  int32_t n, rank, ok;
+  uint32_t head, base;
+};
+
+__device__ __forceinline__ uint32_t agent_load(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int32_t agent_load(const int32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long agent_load(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ void agent_store(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The totals of a burst level: vertices found, their out-edges and in-edges, edges read, vertices
+// past the LDS lists; largest: out-degree, size of one member's part.
+enum { kTotWon, kTotMnew, kTotInsub, kTotEdges, kTotSpilled, kTotMaxdeg, kTotPart, kTotWords };
+struct BurstTotals {
+  uint32_t v[kTotWords];
+};
+
+// Whether level st, of at most mf out-edges and none above maxdeg in one row, is one for n members.
+__device__ __forceinline__ bool burst_fits(const LevelState& st, uint32_t mf, uint32_t maxdeg, uint32_t n) {
+  return !st.done && st.dir == 0 && st.local == 1 && st.phase == kPhaseWhole && uint32_t(st.nf) <= kBurstNf * n &&
+         mf <= kBurstEdges * n && maxdeg <= kBurstDeg;
+}
+
+// The size of a part of a frontier, in vertices of kBurstMapDeg edges: what a member's rounds go by.
+__device__ __forceinline__ uint32_t burst_part(uint32_t vertices, uint32_t edges) {
+  return max(vertices, edges / uint32_t(kBurstMapDeg));
+}
+
+// Joins step s's burst (all threads of a candidate block). False: too late.
+__device__ __forceinline__ bool burst_join(Ctrl* c, int32_t s, BurstShared& sh) {
+  if (threadIdx.x == 0) {
+    BurstCtl& b = c->burst;
+    uint32_t* joined = &b.joined[s % kSlots][0];
+    unsigned long long* members = &b.members[s % kSlots][0];
+    sh.rank = -1;
+    sh.ok = 1;
+    if (blockIdx.x == 0) {
+      for (uint32_t p = 0; p < kBurstJoinPolls && agent_load(joined) < uint32_t(kBurstBlocks - 1); ++p) {}
+      const uint32_t got = __hip_atomic_fetch_or(joined, kBurstClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sh.n = int32_t(min(got, uint32_t(kBurstBlocks - 1))) + 1;
+      sh.rank = 0;
+      sh.head = agent_load(&b.head);
+      agent_store(members, (unsigned long long)uint32_t(sh.n) | ((unsigned long long)sh.head << 32));
+    } else {
+      const uint32_t t = __hip_atomic_fetch_add(joined, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!(t & kBurstClosed)) {
+        unsigned long long m = 0;
+        for (uint32_t p = 0; p < kBurstSpin && m == 0; ++p) m = agent_load(members);
+        sh.n = int32_t(uint32_t(m));
+        sh.head = uint32_t(m >> 32);
+        sh.rank = m ? int32_t(t) + 1 : -1;
+        if (!m) __hip_atomic_fetch_or(&c->bar.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
+  if (threadIdx.x < 2 * kBurstWords) (&sh.red[0][0])[threadIdx.x] = 0;
+  if (threadIdx.x < 2) sh.nbuf[threadIdx.x] = 0;
+  __syncthreads();
+  return sh.rank >= 0;
+}
+
+// Up to kExpandEPT edges a thread works on at once: targets, sources, and the targets' visited
+// words and row extents.
+struct BurstEdges {
+  int32_t w[kExpandEPT], u[kExpandEPT], rb[kExpandEPT], re[kExpandEPT];
+  uint32_t seen[kExpandEPT];
+  int32_t n;  // edges in use
+};
+struct BurstAcc {
+  uint32_t mnew = 0, insub = 0, edges = 0, spilled = 0, maxdeg = 0;
+};
+
+// The claims of level L (all threads call), results, and the winners' entries in the list of
+// parity q. base: where the append counter stood when the level began.
+__device__ __forceinline__ void burst_claim(const BfsArgs& a, uint32_t* claim, int32_t L, uint32_t base, int q,
+                                            BurstShared& sh, const BurstEdges& x, BurstAcc& acc) {
+  uint32_t old[kExpandEPT];
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) {
+    const uint32_t bit = 1u << (x.w[t] & 31);
+    old[t] = 0xffffffffu;
+    if (t < x.n && !(x.seen[t] & bit)) old[t] = atomicOr(claim + (x.w[t] >> 5), bit);
+  }
+  uint32_t c = 0;
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) c += (old[t] & (1u << (x.w[t] & 31))) ? 0u : 1u;
+  if (!__any(c != 0)) return;
+  const uint32_t incl = wave_scan_dpp(c, OpAdd{});
+  uint32_t p = 0;
+  if (lane() == 63) p = atomicAdd(&sh.nbuf[q], incl);
+  p = lane63(p) + incl - c;
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) {
+    const int32_t w = x.w[t];
+    if (old[t] & (1u << (w & 31))) continue;
+    a.depth[w] = L + 1;
+    if (a.parent) a.parent[w] = x.u[t];
+    const uint32_t d = uint32_t(x.re[t] - x.rb[t]);
+    if (p < uint32_t(kBurstCap)) {
+      sh.list[q].v[p] = w;
+      sh.list[q].beg[p] = x.rb[t];
+      sh.list[q].deg[p] = int32_t(d);
+    } else {
+      const uint32_t at =
+          __hip_atomic_fetch_add(&a.ctrl->burst.head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - base;
+      agent_store(&a.Q[(L + 1) % 2][at], w);
+      ++acc.spilled;
+    }
+    ++p;
+    acc.mnew += d;
+    acc.maxdeg = max(acc.maxdeg, d);
+    if (a.edge_rule && a.colptr != a.rowptr) acc.insub += uint32_t(a.colptr[w + 1] - a.colptr[w]);
+  }
+}
+
+// The visited words and row extents of x's targets.
+__device__ __forceinline__ void burst_look(const BfsArgs& a, const uint32_t* claim, BurstEdges& x) {
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) {
+    x.seen[t] = 0;
+    x.rb[t] = x.re[t] = 0;
+    if (t < x.n) {
+      x.seen[t] = claim[x.w[t] >> 5];
+      x.rb[t] = a.rowptr[x.w[t]];
+      x.re[t] = a.rowptr[x.w[t] + 1];
+    }
+  }
+}
+
+// The kExpandEPT edges of this thread when each of the list's nc vertices (at most kThreads / 2)
+// has at most kBurstMapDeg: two threads a vertex.
+__device__ __forceinline__ void burst_fetch_map(const BfsArgs& a, const uint32_t* claim, const BurstList& l, int32_t nc,
+                                                BurstEdges& x) {
+  const int32_t i = int32_t(threadIdx.x) >> 1;
+  int32_t b = 0, d = 0, u = 0;
+  if (i < nc) {
+    const int32_t e0 = (int32_t(threadIdx.x) & 1) * kExpandEPT;
+    u = l.v[i];
+    b = l.beg[i] + e0;
+    d = l.deg[i] - e0;
+  }
+  x.n = min(max(d, 0), kExpandEPT);
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) {
+    x.u[t] = u;
+    x.w[t] = t < x.n ? a.colind[b + t] : 0;
+  }
+  burst_look(a, claim, x);
+}
+
+// Expands the list's nc vertices, whatever their degrees: kThreads of them at a time, their edges
+// shared out by a search over their degree prefix (all threads).
+__device__ __forceinline__ void burst_expand(const BfsArgs& a, uint32_t* claim, int32_t L, uint32_t base, int q,
+                                             const BurstList& l, int32_t nc, BurstShared& sh, BurstAcc& acc) {
+  const int tid = threadIdx.x;
+  for (int32_t u0 = 0; u0 < nc; u0 += kThreads) {
+    const int32_t cnt = min(nc - u0, kThreads);
+    uint32_t total;
+    const uint32_t ex = block_excl_scan(tid < cnt ? uint32_t(l.deg[u0 + tid]) : 0u, &total);
+    sh.off[tid] = int32_t(ex);
+    __syncthreads();
+    for (uint32_t e0 = 0; e0 < total; e0 += kExpandChunk) {
+      BurstEdges x;
+      const uint32_t e1 = e0 + uint32_t(tid);
+      x.n = e1 < total ? int32_t(min((total - e1 + kThreads - 1) / kThreads, uint32_t(kExpandEPT))) : 0;
+#pragma unroll
+      for (int t = 0; t < kExpandEPT; ++t) {
+        x.w[t] = x.u[t] = 0;
+        if (t < x.n) {
+          const uint32_t e = e1 + uint32_t(t * kThreads);
+          const int32_t k = thread_search(sh.off, 0, cnt, e);
+          x.u[t] = l.v[u0 + k];
+          x.w[t] = a.colind[l.beg[u0 + k] + int32_t(e - uint32_t(sh.off[k]))];
+        }
+      }
+      burst_look(a, claim, x);
+      burst_claim(a, claim, L, base, q, sh, x, acc);
+    }
+    __syncthreads();  // off is free for the next vertices
+  }
+}
+
+// Appends this member's part of level L + 1's frontier (nc vertices of the list of parity q) to the
+// list in memory (all threads).
+__device__ __forceinline__ void burst_flush(const BfsArgs& a, int32_t L, uint32_t base, const BurstList& l, int32_t nc,
+                                            BurstShared& sh) {
+  if (threadIdx.x == 0 && nc)
+    sh.base = __hip_atomic_fetch_add(&a.ctrl->burst.head, uint32_t(nc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - base;
+  __syncthreads();
+  int32_t* Qn = a.Q[(L + 1) % 2];
+  for (int32_t i = threadIdx.x; i < nc; i += kThreads) agent_store(&Qn[sh.base + uint32_t(i)], l.v[i]);
+}
+
+// The word of the members' records that this thread looks at in burst_gather.
+__device__ __forceinline__ const unsigned long long* burst_word(Ctrl* c, int buf) {
+  return &c->burst.rec[buf][threadIdx.x >> 3][threadIdx.x & 7];
+}
+
+// Waits until every member has left its words with this tag and combines them (all threads; ends
+// past a barrier). x: this thread's word as loaded before. False: a wait gave up.
+__device__ __forceinline__ bool burst_gather(Ctrl* c, int buf, uint32_t tag, unsigned long long x, BurstShared& sh,
+                                             BurstTotals* out) {
+  static_assert(kThreads / 64 == 4, "four partial values a word");
+  const int tid = threadIdx.x;
+  const int m = tid >> 3, word = tid & 7;
+  uint32_t v = 0;
+  if (m < sh.n && word < kTotWords) {
+    for (uint32_t k = 0; uint32_t(x >> 32) != tag && k < kBurstSpin; ++k) x = agent_load(burst_word(c, buf));
+    if (uint32_t(x >> 32) != tag) {
+      sh.ok = 0;
+      __hip_atomic_fetch_or(&c->bar.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    v = uint32_t(x);
+  }
+#pragma unroll
+  for (int d = 8; d < 64; d *= 2) {
+    const uint32_t o = uint32_t(__shfl_xor(int(v), d, 64));
+    v = word >= kTotMaxdeg ? max(v, o) : v + o;
+  }
+  if (lane() < kBurstWords) sh.tot[lane()][tid >> 6] = v;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kTotWords; ++k) {
+    const uint4 t = *reinterpret_cast<const uint4*>(&sh.tot[k][0]);
+    const uint32_t r = k >= kTotMaxdeg ? max(max(t.x, t.y), max(t.z, t.w)) : t.x + t.y + t.z + t.w;
+    out->v[k] = __builtin_amdgcn_readfirstlane(r);
+  }
+  return sh.ok != 0;
+}
+
+// The state entering the level after st, given st's totals: what next_state makes of them for a
+// list push, without the share of a push that k_step runs (the step after a burst derives the
+// state anew). local is exact: whether the level could share out its own work.
+__device__ __forceinline__ LevelState burst_next(const BfsArgs& a, int32_t forced, const LevelState& st,
+                                                 const BurstTotals& t) {
+  LevelState next = st;
+  next.level = st.level + 1;
+  if (t.v[kTotWon] == 0) {
+    next.done = 1;
+    next.levels = next.level;
+    return next;
+  }
+  next.m_u = st.m_u - (a.edge_rule ? int64_t(t.v[kTotInsub]) : 0);
+  next.dir = next_direction_rule(a.heuristic, a.alpha, a.beta, 0, a.V, st.nf, int64_t(t.v[kTotWon]),
+                                 int64_t(t.v[kTotMnew]), next.m_u);
+  if (a.mode == 1) next.dir = 0;  // push only
+  if (a.mode == 5) next.dir = 1;  // pull only
+  if (forced >= 0) next.dir = forced;
+  next.nf = int32_t(t.v[kTotWon]);
+  next.list_valid = 1;
+  // (a unit never has more chunks than its edges need: the divisions of local_fits are rarely made)
+  const bool local = a.low_degree ||
+                     local_unit_chunks_bound(t.v[kTotMnew], t.v[kTotMaxdeg], a.sched.local_unit) <=
+                         uint32_t(a.sched.local_chunks) ||
+                     local_fits(next.nf, t.v[kTotMnew], t.v[kTotMaxdeg], main_blocks(a.nwords), a.sched.local_unit,
+                                a.sched.local_chunks);
+  next.local = next.dir == 0 && local ? 1 : 0;
+  next.phase = next.dir == 0 && !local ? kPhaseScan : kPhaseWhole;
+  return next;
+}
+
+// Step s from its level st on (candidate blocks): levels while they fit and stay below level_end.
+// Block 0 leaves what a step that ran the last of them alone would leave (its state, its counters,
+// the records of the levels before), or, when the traversal ended, the final state; then the
+// report, when the step has one to write.
+__device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32_t s, const StepReportArgs& rp,
+                                          BurstShared& sh) {
+  Ctrl* c = a.ctrl;
+  if (!burst_join(c, s, sh)) return;
+  const int tid = threadIdx.x;
+  const uint32_t n = uint32_t(sh.n), r = uint32_t(sh.rank);
+  uint32_t* claim = a.vis[st.vis_idx];
+  uint32_t base = sh.head;
+  int buf = 0;
+  int32_t nc = 0;            // vertices of this level in the list of its parity
+  bool listed = true;        // the frontier is in memory (else in the members' lists)
+  bool fetched = false;      // x holds this level's edges
+  uint32_t m_f = 0;          // out-edges of the frontier (of one kept in the lists)
+  BurstEdges x;
+  bool failed = false;
+  while (true) {
+    const int32_t L = st.level;
+    const int p = L & 1, q = p ^ 1;
+    BurstAcc acc;
+    if (listed) {  // this member's part of the list in memory, kBurstCap vertices at a time
+      const uint32_t nf = uint32_t(st.nf), per = (nf + n - 1) / n;
+      const uint32_t lo = min(r * per, nf), hi = min(lo + per, nf);
+      const int32_t* Q = a.Q[p];
+      for (uint32_t i0 = lo; i0 < hi; i0 += kBurstCap) {
+        nc = int32_t(min(hi - i0, uint32_t(kBurstCap)));
+        for (int32_t i = tid; i < nc; i += kThreads) {
+          const int32_t u = agent_load(&Q[i0 + uint32_t(i)]);
+          const int32_t b = a.rowptr[u], d = a.rowptr[u + 1] - b;
+          sh.list[p].v[i] = u;
+          sh.list[p].beg[i] = b;
+          sh.list[p].deg[i] = d;
+          acc.edges += uint32_t(d);
+        }
+        __syncthreads();
+        burst_expand(a, claim, L, base, q, sh.list[p], nc, sh, acc);
+        __syncthreads();
+      }
+    } else if (fetched) {
+      burst_claim(a, claim, L, base, q, sh, x, acc);
+    } else {
+      burst_expand(a, claim, L, base, q, sh.list[p], nc, sh, acc);
+    }
+    // this block's totals (the vertices found are counted in nbuf)
+    {
+      auto add = [&](int k, uint32_t v) {
+        v = wave_sum(v);
+        if (lane() == 0 && v) atomicAdd(&sh.red[p][k], v);
+      };
+      if (__any(acc.mnew != 0)) {
+        add(kTotMnew, acc.mnew);
+        const uint32_t v = wave_max32(acc.maxdeg);
+        if (lane() == 0) atomicMax(&sh.red[p][kTotMaxdeg], v);
+      }
+      if (a.edge_rule && a.colptr != a.rowptr) add(kTotInsub, acc.insub);
+      if (listed) add(kTotEdges, acc.edges);
+      if (__any(acc.spilled != 0)) add(kTotSpilled, acc.spilled);
+    }
+    __syncthreads();  // the totals stand, and every claim has returned
+    if (tid == kBurstWords) sh.nbuf[p] = 0;  // last read a level ago, next counted in at the next level
+    const uint32_t tag = 2u * uint32_t(L) + 1u;
+    const uint32_t found = sh.nbuf[q];
+    if (tid < kTotWords) {
+      uint32_t v = sh.red[p][tid];
+      if (tid == kTotWon) v = found;
+      if (tid == kTotInsub && a.colptr == a.rowptr) v = sh.red[p][kTotMnew];
+      if (tid == kTotPart) v = burst_part(found, sh.red[p][kTotMnew]);
+      agent_store(&c->burst.rec[buf][r][tid], ((unsigned long long)tag << 32) | v);
+    }
+    unsigned long long seen_word = agent_load(burst_word(c, buf));
+    nc = int32_t(min(found, uint32_t(kBurstCap)));
+    // what the next level can do before the others are through
+    fetched = sh.red[p][kTotMaxdeg] <= uint32_t(kBurstMapDeg) && nc <= kThreads / 2;
+    if (fetched) burst_fetch_map(a, claim, sh.list[q], nc, x);
+    BurstTotals t;
+    if (!burst_gather(c, buf, tag, seen_word, sh, &t)) {
+      failed = true;
+      break;
+    }
+    buf ^= 1;
+    if (tid < kBurstWords) sh.red[p][tid] = 0;  // next used two levels on
+    // a level whose frontier stayed in the members' lists reads the out-edges found the level before
+    if (!listed) t.v[kTotEdges] = m_f;
+    m_f = t.v[kTotMnew];
+    const int32_t forced = L + 1 < a.n_forced ? int32_t(c->forced[L + 1]) : -1;
+    const LevelState next = burst_next(a, forced, st, t);
+    const bool go_on = burst_fits(next, t.v[kTotMnew], t.v[kTotMaxdeg], n) && L + 1 < rp.level_end;
+    if (r == 0 && tid == 0) {
+      if (go_on || next.done) {
+        LevelTotals tot{t.v[kTotWon], 0, t.v[kTotEdges], t.v[kTotMnew], t.v[kTotInsub], 0};
+        c->rec[L % kRing] = step_record(c, s, st, tot);
+      }
+      if (!go_on) {
+        if (next.done)
+          c->ring[s % kRing] = next;
+        else
+          c->ring[s % kRing] = st;
+        Stripe& z = c->slot[s % kSlots].s[0];
+        z.count = t.v[kTotWon];
+        z.mnew = t.v[kTotMnew];
+        z.insub = t.v[kTotInsub];
+        z.edges = t.v[kTotEdges];
+        z.maxdeg = t.v[kTotMaxdeg];
+      }
+    }
+    // shared out anew when a list overflowed, or when one member's part takes more than one round
+    // of its threads and is half again the average
+    listed = t.v[kTotSpilled] != 0 ||
+             (t.v[kTotPart] > kBurstNf && t.v[kTotPart] * n * 2u > 3u * burst_part(t.v[kTotWon], t.v[kTotMnew]));
+    if (!next.done && (listed || !go_on)) burst_flush(a, L, base, sh.list[q], nc, sh);
+    if (!go_on) {
+      if (next.done) st = next;
+      break;
+    }
+    if (listed) {
+      __builtin_amdgcn_s_waitcnt(0);  // this wave's list entries are complete
+      __syncthreads();
+      if (tid < kTotWords) agent_store(&c->burst.rec[buf][r][tid], (unsigned long long)(tag + 1u) << 32);
+      BurstTotals none;
+      if (!burst_gather(c, buf, tag + 1u, 0ull, sh, &none)) {
+        failed = true;
+        break;
+      }
+      buf ^= 1;
+    }
+    base += t.v[kTotWon] * uint32_t(listed);
+    st = next;
+  }
+  if (r == 0 && rp.host) {
+    __syncthreads();
+    step_report(c, rp, s, st, st, LevelTotals{0, 0, 0, 0, 0, 0}, false, failed ? 1 : 0);
+  }
+}
+
+// kBurst: the form that may run a burst. It needs more registers than the others' LDS leaves
+// wavefronts for (4 blocks per CU instead of 6), so the host launches it where it expects narrow
+// levels (SingleSteps::burst_form); either form is right for any level.
+template <bool EE, bool kBurst>
 __global__ __launch_bounds__(kThreads) void k_step(BfsArgs a, int32_t s, StepReportArgs rp) {
-  __shared__ LevelShared sh;
+  __shared__ union {
+    LevelShared l;
+    BurstShared b;
+  } sh;
   LevelTotals tot;
   LevelState prev;
   bool new_level;
   const LevelState st = step_state(a, s, &tot, &prev, &new_level);
+  const bool burst = kBurst && burst_fits(st, uint32_t(st.active >> 32), uint32_t(st.active), kBurstBlocks);
   if (blockIdx.x == 0) {
     publish_step(a.ctrl, s, st, prev, tot, new_level);
-    if (rp.host) step_report(a.ctrl, rp, s, st, prev, tot, new_level, 0);
+    if (rp.host && !burst)
+      step_report(a.ctrl, rp, s, st, prev, tot, new_level, int32_t(a.ctrl->bar.abort != 0));
   }
   if (st.done) return;
-  step_body<EE>(a, st, s, sh, int32_t(blockIdx.x), int32_t(gridDim.x));
+  if (burst) {
+    // consecutive blocks go to the XCDs in turn: every eighth sits on the leader's
+    if (blockIdx.x % 8 == 0 && blockIdx.x < 8 * kBurstBlocks) burst_run(a, st, s, rp, sh.b);
+    return;
+  }
+  step_body<EE>(a, st, s, sh.l, int32_t(blockIdx.x), int32_t(gridDim.x));
 }
 
 
@@ -1085,7 +1555,7 @@ __global__ void k_step_report(const Ctrl* c, int32_t s_first, int32_t n, int32_t
   for (int k = threadIdx.x; k < n; k += blockDim.x) host->steps[k] = c->ring[(s_first + k) % kRing];
   const LevelState end = c->ring[(s_first + n - 1) % kRing];
   const int32_t upto = end.done ? end.levels : end.level;  // records exist for levels < upto
-  const int32_t nrec = max(0, min(upto - rec_first, kMaxBatch));
+  const int32_t nrec = max(0, min(upto - rec_first, kMaxRec));
   for (int k = threadIdx.x; k < nrec; k += blockDim.x) host->rec[k] = c->rec[(rec_first + k) % kRing];
   if (threadIdx.x == 0) {
     host->end = end;
@@ -1270,11 +1740,12 @@ hipError_t launch_level_prep(hipStream_t s, const BfsArgs& a, int32_t level, int
 }
 
 hipError_t launch_step(hipStream_t s, const BfsArgs& a, int32_t step, hipEvent_t t0, hipEvent_t t1,
-                       const StepReportArgs* rp) {
+                       const StepReportArgs& rp, bool burst) {
   const dim3 g(unsigned(main_blocks(a.nwords)));
-  const StepReportArgs r = rp ? *rp : StepReportArgs{nullptr, 0u, 0, 0};
-  if (a.early_exit) return launch_k(k_step<true>, g, s, t0, t1, a, step, r);
-  return launch_k(k_step<false>, g, s, t0, t1, a, step, r);
+  const StepReportArgs r = rp;
+  if (a.early_exit && burst) return launch_k(k_step<true, true>, g, s, t0, t1, a, step, r);
+  if (a.early_exit) return launch_k(k_step<true, false>, g, s, t0, t1, a, step, r);
+  return launch_k(k_step<false, false>, g, s, t0, t1, a, step, r);
 }
 
 hipError_t launch_steps(hipStream_t s, const BfsArgs& a, int32_t s_first, int32_t n, int32_t blocks,

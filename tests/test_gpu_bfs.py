@@ -506,3 +506,76 @@ def test_permutation_invariance(graphs):
     r2.run(int(perm[s]))
     d1, d2 = r1.result()[0], r2.result()[0]
     assert np.array_equal(d2[perm], d1)
+
+
+def _comb(d, tail, directed):
+    """A hub with d teeth, each a path of `tail` vertices; neighbouring teeth joined at the third
+    vertex, so that later levels have claims from two sides."""
+    first = 1 + np.arange(d) * tail
+    src = [np.zeros(d, dtype=np.int64)]
+    dst = [first]
+    for k in range(tail - 1):
+        src.append(first + k)
+        dst.append(first + k + 1)
+    if tail > 3 and d > 1:
+        src.append(first[:-1] + 2)
+        dst.append(first[1:] + 3)
+    return gen.from_edges(1 + d * tail, np.concatenate(src), np.concatenate(dst), directed=directed,
+                          name="comb%dx%d" % (d, tail))
+
+
+@pytest.mark.parametrize("d", [1, 31, 127, 129, 511, 513, 1024, 1025, 4095, 4097])
+def test_narrow_levels_in_one_launch(d):
+    """Consecutive narrow push levels run in one launch: hubs of d neighbours take one member's part
+    past a round of its threads, past what it keeps on chip (512) and past the largest out-degree
+    (1024) and frontier (4096) of such a level, so levels are kept, shared out anew and handed back
+    to the other form. Depths, parents and every level's counts equal the oracle's, and the
+    step-per-level run's (timed calls)."""
+    for directed in (False, True):
+        hg = _comb(d, 6, directed)
+        g = upload(hg)
+        r = BfsRunner(g)
+        for s in (0, 1 + 6 * (d // 2) + 5 if not directed else 1):
+            want, _ = oracle.bfs(hg, s)
+            sizes, outdeg = oracle.level_sizes(want), hg.out_degree()
+            for kw in (dict(mode="push_only"), dict(heuristic=dobfs.HEUR_EDGES, alpha=1e30, beta=0.0),
+                       dict(mode="full"), dict(forced_dirs=[PUSH, PUSH, PULL, PUSH, PUSH])):
+                tag = "%s directed=%s src=%d %s" % (hg.name, directed, s, kw)
+                r.run(s, **kw)
+                depth, parent = r.result()
+                lv = r.levels()
+                assert np.array_equal(depth, want), tag
+                assert oracle.validate(hg, s, depth, parent)[0] == 0, tag
+                assert [x["nf"] for x in lv] == sizes, tag
+                for L, x in enumerate(lv):
+                    assert x["n_new"] == int((want == L + 1).sum()), tag
+                    if x["dir"] == PUSH:
+                        assert x["edges"] == x["m_f"] == int(outdeg[want == L].sum()), tag
+                key = [(x["dir"], x["variant"]) for x in lv]
+                r.run(s, time_kernels=True, **kw)
+                assert [(x["dir"], x["variant"]) for x in r.levels()] == key, tag
+        dobfs.graph_destroy(g)
+
+
+def test_narrow_levels_deep():
+    """More levels than one report holds records for (a path of 5000 vertices, a 1500 x 3 grid),
+    with and without statistics, and schedule settings that change which pushes need no scan."""
+    path = gen.from_edges(5000, np.arange(4999), np.arange(1, 5000), directed=False, name="path5000")
+    for hg in (path, gen.grid2d(1500, 3)):
+        g = upload(hg)
+        r = BfsRunner(g, stats_cap=8192)
+        depth = torch.empty(g.V, dtype=torch.int32, device="cuda")
+        for s in (0, g.V // 2):
+            want, _ = oracle.bfs(hg, s)
+            for sched in (None, {"local_unit": 1, "local_chunks": 1}):
+                opt = dobfs.make_options(heuristic=dobfs.HEUR_EDGES, alpha=1 / 14, beta=0.0, sched=sched)
+                r.run(s, opt=opt)
+                d, p = r.result()
+                assert np.array_equal(d, want) and oracle.validate(hg, s, d, p)[0] == 0, hg.name
+                lv = r.levels()
+                assert [x["nf"] for x in lv] == oracle.level_sizes(want), hg.name
+                assert r.stats.reached == g.V and r.stats.levels == len(lv), hg.name
+                depth.fill_(-7)
+                dobfs.bfs(g, s, depth, None, opt)
+                assert np.array_equal(depth.cpu().numpy(), want), hg.name
+        dobfs.graph_destroy(g)
