@@ -164,7 +164,8 @@ typedef struct {
   int32_t pull_mid;          /* pull: in-neighbours a thread scans before a wave of 64 lanes takes
                                 the row over, 4 .. 2^20 (default 32) */
   int32_t bitmap_rows;       /* push after a pull runs block-local over the pull's bits when no
-                                4096-row tile found more rows than this, 0 .. 4096 (default 512) */
+                                tile (4096 rows, fewer on graphs below 4 M vertices) found more
+                                rows than this, 0 .. 4096 (default 512) */
   int32_t local_unit;        /* block-local push: frontier vertices a block takes at once,
                                 1 .. 256 (default 128) */
   int32_t local_chunks;      /* block-local push: most 1024-edge chunks of a unit one block may

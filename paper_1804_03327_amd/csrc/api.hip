@@ -493,6 +493,7 @@ BfsArgs bfs_args(dobfs_graph g, uint8_t* ws, const Layout& L, const dobfs_option
   a.local_push = a.need_F ? 0 : 1;  // (the frontier bitmap a push writes is cleared by its scan step)
   a.low_degree = g->max_outdeg <= uint32_t(kLocalDeg) ? 1 : 0;
   a.max_outdeg = g->max_outdeg;
+  a.pull_words = pull_tile_words(g->nwords);
   a.sched = default_sched();
   if (opt.pull_mid) a.sched.pull_mid = opt.pull_mid;
   if (opt.bitmap_rows) a.sched.bitmap_rows = opt.bitmap_rows;
@@ -1373,6 +1374,7 @@ dobfs_status dobfs_mxv(dobfs_graph g, const uint32_t* x_bits, const int32_t* x_i
     PullArgs pa{};
     pa.V = V;
     pa.nwords = nwords;
+    pa.tile_words = pull_tile_words(nwords);
     pa.colptr = g->colptr;
     pa.rowind = g->rowind;
     pa.slab = g->slab;

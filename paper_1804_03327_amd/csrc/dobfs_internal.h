@@ -154,8 +154,9 @@ constexpr int kExpandChunk = kThreads * kExpandEPT; // 1024 edges per chunk
 constexpr int kExpandWin = kExpandChunk + 1;         // frontier entries cached in LDS per chunk
 constexpr int kExpandBuf = 2048;                     // winners buffered in LDS before a list flush
 constexpr int kExpandBlocks = 1024;                  // expand grid (strides over chunks)
-constexpr int kPullTileWords = 128;                  // pull: bitmap words owned by a block (measured
+constexpr int kPullTileWords = 128;                  // pull: most bitmap words owned by a block (measured
                                                      // best of 8..256 on RMAT-22: fewer, fuller blocks)
+constexpr int kPullTileMin = 8;                      // fewest: 256 rows, one per thread
 constexpr int kPullTileV = kPullTileWords * 32;      // 4096 rows per block
 constexpr int kSlab = 4;                             // in-neighbours per row kept in the dense slab
 constexpr int kPullFirst = kSlab;                    // pull phase 1 checks a row's slab entries
@@ -173,6 +174,17 @@ inline int64_t scan_tiles(int64_t n) { return (n + kScanTile - 1) / kScanTile; }
 inline int64_t bits_tiles(int64_t nwords) { return (nwords + kBitsTile - 1) / kBitsTile; }
 __host__ __device__ inline int64_t pull_tiles(int64_t nwords) {
   return (nwords + kPullTileWords - 1) / kPullTileWords;
+}
+// Bitmap words of a pull tile: kPullTileWords, halved while that leaves the graph fewer than
+// kExpandBlocks tiles (about what the chip holds at once). A pull is bound by its chains of
+// dependent loads: with 128-word tiles a graph of a million vertices had one block per CU, one of a
+// thousand a single block. A matvec by rows over RMAT-20 (early exit, 5% of the vertices in x)
+// 108 -> 75 us, a tree of 750 000 vertices 432 -> 411 us per search; half as many, larger tiles gave
+// 85 and 421 us.
+__host__ __device__ inline int32_t pull_tile_words(int64_t nwords) {
+  int32_t w = kPullTileMin;
+  while (w < kPullTileWords && (nwords + w - 1) / w > kExpandBlocks) w *= 2;
+  return w;
 }
 // Blocks of a level's second kernel: the pull's tiles, at least the push's expand grid.
 __host__ __device__ inline int64_t main_blocks(int64_t nwords) {
@@ -234,6 +246,7 @@ inline int32_t scan_grid(int64_t V) {
 // ---- argument blocks ----
 struct PullArgs {
   int32_t V, nwords;
+  int32_t tile_words;        // pull_tile_words(nwords)
   const int32_t* colptr;
   const int32_t* rowind;
   const int4* slab;          // first kSlab entries of every CSC column (-1 past its end)
@@ -323,6 +336,7 @@ struct BfsArgs {
   int32_t low_degree;        // every out-degree of the graph is <= kLocalDeg
   int32_t n_forced;          // levels whose direction Ctrl::forced fixes
   uint32_t max_outdeg;       // largest out-degree of the graph
+  int32_t pull_words;        // pull_tile_words(nwords)
   Sched sched;
 };
 

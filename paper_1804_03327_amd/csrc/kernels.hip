@@ -419,7 +419,7 @@ struct PullShared {
 };
 
 // Row-based masked matvec (Algorithm 2) over CSC(A) for the rows of one
-// tile of kPullTileWords bitmap words: list the rows the mask lets through
+// tile of bitmap words (pull_tile_words): list the rows the mask lets through
 // (output sparsity, Section 5.2) and check each row's in-neighbours in stored
 // order, stopping at the first hit (early exit, Section 5.3). The phases
 // keep many loads in flight: every candidate's first in-neighbour from the
@@ -436,7 +436,8 @@ struct PullShared {
 template <bool EE>
 __device__ __forceinline__ void pull_body(const PullArgs& a, int32_t tile, PullShared& sh) {
   const int tid = threadIdx.x;
-  const int32_t w0 = tile * kPullTileWords;
+  const int32_t tw = a.tile_words;
+  const int32_t w0 = tile * tw;
   const int32_t v0 = w0 * 32;
   const uint32_t cflip = a.complement ? 0xffffffffu : 0u;
 
@@ -448,7 +449,7 @@ __device__ __forceinline__ void pull_body(const PullArgs& a, int32_t tile, PullS
     const int32_t w = w0 + lw;
     if (half == 0) sh.found[lw] = 0;
     uint32_t cw = 0;
-    if (w < a.nwords) {
+    if (lw < tw && w < a.nwords) {
       const uint32_t pass = a.mask ? (a.mask[w] ^ cflip) : 0xffffffffu;
       cw = (a.mask_after ? 0xffffffffu : pass) & a.nz[w] & valid_bits(w, a.V);
       cw = half ? (cw >> 16) : (cw & 0xffffu);
@@ -632,7 +633,7 @@ __device__ __forceinline__ void pull_body(const PullArgs& a, int32_t tile, PullS
   __syncthreads();
 
   unsigned long long nfound = 0, nout = 0, nheavy = 0;
-  for (int lw = tid; lw < kPullTileWords; lw += kThreads) {
+  for (int lw = tid; lw < tw; lw += kThreads) {
     const int32_t w = w0 + lw;
     if (w < a.nwords) {
       const uint32_t f = sh.found[lw];
@@ -985,11 +986,12 @@ __device__ __forceinline__ void step_body(const BfsArgs& a, const LevelState& st
       local_expand_body(e, sh.l, bid, nblk);
     }
   } else {
-    const int32_t tiles = (a.nwords + kPullTileWords - 1) / kPullTileWords;
+    const int32_t tiles = (a.nwords + a.pull_words - 1) / a.pull_words;
     if (bid >= tiles) return;
     PullArgs p;
     p.V = a.V;
     p.nwords = a.nwords;
+    p.tile_words = a.pull_words;
     p.colptr = a.colptr;
     p.rowind = a.rowind;
     p.slab = a.slab;
@@ -1793,7 +1795,7 @@ hipError_t launch_expand(hipStream_t s, const ExpandArgs& a, const uint32_t* m_d
 }
 
 hipError_t launch_pull(hipStream_t s, const PullArgs& a) {
-  const unsigned g = unsigned(pull_tiles(a.nwords));
+  const unsigned g = unsigned((a.nwords + a.tile_words - 1) / a.tile_words);
   if (a.early_exit)
     hipLaunchKernelGGL(k_pull<true>, dim3(g), dim3(kThreads), 0, s, a);
   else
