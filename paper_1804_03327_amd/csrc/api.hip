@@ -566,12 +566,13 @@ struct SingleSteps {
   static int32_t capacity(const PersistentDevice& d) { return d.capacity; }
   hipError_t step(hipStream_t s, int32_t k, int64_t, bool narrow, hipEvent_t t0, hipEvent_t t1,
                   const StepReportArgs& rp) const {
-    return launch_step(s, a, k, t0, t1, rp, burst && (narrow || k == 0));
+    return launch_step(s, a, k, t0, t1, rp, burst && (narrow || (k == 0 && a.max_outdeg <= kBurstDeg)));
   }
   // Whether launches are given the form that runs several narrow levels at once: the first launch
-  // always (a traversal starts at one vertex), the rest of the first batch on graphs without hubs
-  // (meshes, roads and trees, whose frontiers stay narrow; where there are hubs the second or third
-  // level is wide already), and later batches as the batch before ended.
+  // unless the graph has hubs that such a level cannot have (the second level is then wide as a
+  // rule, and RMAT-22 lost 1% to the form that handles the first), the rest of the first batch on
+  // graphs of low degree (meshes, roads and trees, whose frontiers stay narrow), and later
+  // batches as the batch before ended.
   bool narrow_first() const { return a.low_degree != 0; }
   bool narrow_next(const HostReport& r) const {
     const LevelState& st = r.end;

@@ -97,6 +97,7 @@ struct GridBar {
 constexpr int kBurstBlocks = 32;      // members at most: about one per CU of an XCD
 constexpr int kBurstWords = 8;
 constexpr uint32_t kBurstNf = 128;    // most frontier vertices of a burst level, per member
+constexpr uint32_t kBurstDeg = 1024;  // largest out-degree (a row is one member's)
 struct BurstCtl {
   alignas(128) uint32_t joined[kSlots][32];          // a line per slot; kBurstClosed: too late
   alignas(128) unsigned long long members[kSlots][16];  // members | head << 32; 0: not yet known

@@ -1043,7 +1043,6 @@ __device__ __forceinline__ void step_body(const BfsArgs& a, const LevelState& st
 // claims, totals. The limits are one round of a member's threads: a wider level would take it two,
 // and the whole chip runs levels of some ten thousand edges as fast.
 constexpr uint32_t kBurstEdges = 1024;       // most out-edges of a burst level, per member
-constexpr uint32_t kBurstDeg = 1024;         // largest out-degree (a row is one member's)
 constexpr int kBurstCap = 512;               // frontier vertices a member keeps in LDS
 constexpr uint32_t kBurstJoinPolls = 16;     // the leader's wait for the candidates (about 4 us)
 constexpr uint32_t kBurstSpin = 1u << 22;    // bound of every other wait (polls)
@@ -1095,15 +1094,23 @@ __device__ __forceinline__ uint32_t burst_part(uint32_t vertices, uint32_t edges
   return max(vertices, edges / uint32_t(kBurstMapDeg));
 }
 
-// Joins step s's burst (all threads of a candidate block). False: too late.
-__device__ __forceinline__ bool burst_join(Ctrl* c, int32_t s, BurstShared& sh) {
+// How many members a burst on this graph is for. Where there are hubs a search is narrow for a
+// level or two and then wide at once: the leader runs those alone, and nobody has to join.
+__device__ __forceinline__ uint32_t burst_members(const BfsArgs& a) { return a.low_degree ? kBurstBlocks : 1; }
+
+// Joins step s's burst, one for `most` members (all threads of a candidate block). False: too late.
+__device__ __forceinline__ bool burst_join(Ctrl* c, int32_t s, uint32_t most, BurstShared& sh) {
   if (threadIdx.x == 0) {
     BurstCtl& b = c->burst;
     uint32_t* joined = &b.joined[s % kSlots][0];
     unsigned long long* members = &b.members[s % kSlots][0];
     sh.rank = -1;
     sh.ok = 1;
-    if (blockIdx.x == 0) {
+    if (most == 1) {
+      sh.n = 1;
+      sh.rank = 0;
+      sh.head = agent_load(&b.head);
+    } else if (blockIdx.x == 0) {
       for (uint32_t p = 0; p < kBurstJoinPolls && agent_load(joined) < uint32_t(kBurstBlocks - 1); ++p) {}
       const uint32_t got = __hip_atomic_fetch_or(joined, kBurstClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       sh.n = int32_t(min(got, uint32_t(kBurstBlocks - 1))) + 1;
@@ -1335,7 +1342,7 @@ __device__ __forceinline__ LevelState burst_next(const BfsArgs& a, int32_t force
 __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32_t s, const StepReportArgs& rp,
                                           BurstShared& sh) {
   Ctrl* c = a.ctrl;
-  if (!burst_join(c, s, sh)) return;
+  if (!burst_join(c, s, burst_members(a), sh)) return;
   const int tid = threadIdx.x;
   const uint32_t n = uint32_t(sh.n), r = uint32_t(sh.rank);
   uint32_t* claim = a.vis[st.vis_idx];
@@ -1393,20 +1400,22 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
     if (tid == kBurstWords) sh.nbuf[p] = 0;  // last read a level ago, next counted in at the next level
     const uint32_t tag = 2u * uint32_t(L) + 1u;
     const uint32_t found = sh.nbuf[q];
+    unsigned long long word = 0;  // this member's, then the one this thread waits for
     if (tid < kTotWords) {
       uint32_t v = sh.red[p][tid];
       if (tid == kTotWon) v = found;
       if (tid == kTotInsub && a.colptr == a.rowptr) v = sh.red[p][kTotMnew];
       if (tid == kTotPart) v = burst_part(found, sh.red[p][kTotMnew]);
-      agent_store(&c->burst.rec[buf][r][tid], ((unsigned long long)tag << 32) | v);
+      word = ((unsigned long long)tag << 32) | v;
+      if (n > 1) agent_store(&c->burst.rec[buf][r][tid], word);
     }
-    unsigned long long seen_word = agent_load(burst_word(c, buf));
+    if (n > 1) word = agent_load(burst_word(c, buf));
     nc = int32_t(min(found, uint32_t(kBurstCap)));
     // what the next level can do before the others are through
     fetched = sh.red[p][kTotMaxdeg] <= uint32_t(kBurstMapDeg) && nc <= kThreads / 2;
     if (fetched) burst_fetch_map(a, claim, sh.list[q], nc, x);
     BurstTotals t;
-    if (!burst_gather(c, buf, tag, seen_word, sh, &t)) {
+    if (!burst_gather(c, buf, tag, word, sh, &t)) {
       failed = true;
       break;
     }
@@ -1448,9 +1457,10 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
     if (listed) {
       __builtin_amdgcn_s_waitcnt(0);  // this wave's list entries are complete
       __syncthreads();
-      if (tid < kTotWords) agent_store(&c->burst.rec[buf][r][tid], (unsigned long long)(tag + 1u) << 32);
+      word = (unsigned long long)(tag + 1u) << 32;
+      if (tid < kTotWords && n > 1) agent_store(&c->burst.rec[buf][r][tid], word);
       BurstTotals none;
-      if (!burst_gather(c, buf, tag + 1u, 0ull, sh, &none)) {
+      if (!burst_gather(c, buf, tag + 1u, n > 1 ? 0ull : word, sh, &none)) {
         failed = true;
         break;
       }
@@ -1478,7 +1488,7 @@ __global__ __launch_bounds__(kThreads) void k_step(BfsArgs a, int32_t s, StepRep
   LevelState prev;
   bool new_level;
   const LevelState st = step_state(a, s, &tot, &prev, &new_level);
-  const bool burst = kBurst && burst_fits(st, uint32_t(st.active >> 32), uint32_t(st.active), kBurstBlocks);
+  const bool burst = kBurst && burst_fits(st, uint32_t(st.active >> 32), uint32_t(st.active), burst_members(a));
   if (blockIdx.x == 0) {
     publish_step(a.ctrl, s, st, prev, tot, new_level);
     if (rp.host && !burst)
@@ -1487,7 +1497,7 @@ __global__ __launch_bounds__(kThreads) void k_step(BfsArgs a, int32_t s, StepRep
   if (st.done) return;
   if (burst) {
     // consecutive blocks go to the XCDs in turn: every eighth sits on the leader's
-    if (blockIdx.x % 8 == 0 && blockIdx.x < 8 * kBurstBlocks) burst_run(a, st, s, rp, sh.b);
+    if (blockIdx.x % 8 == 0 && blockIdx.x < 8 * burst_members(a)) burst_run(a, st, s, rp, sh.b);
     return;
   }
   step_body<EE>(a, st, s, sh.l, int32_t(blockIdx.x), int32_t(gridDim.x));
