@@ -349,8 +349,10 @@ __device__ void scan_bits(const ScanBitsArgs& a) {
     for (int k = 0; k < kBitsWPT; ++k) {
       const int32_t w = wbase + k;
       bits[k] = 0;
-      if (w < a.nwords)
-        bits[k] = a.a[w] & (a.b_not ? ~a.b_not[w] : 0xffffffffu) & valid_bits(w, a.V);
+      if (w < a.nwords) {
+        bits[k] = ((a.a[w] & (a.b_not ? ~a.b_not[w] : 0xffffffffu)) | (a.b_or ? a.b_or[w] : 0u)) & valid_bits(w, a.V);
+        if (a.words_out) a.words_out[w] = bits[k];
+      }
       c += __popc(bits[k]);
       if (a.rowptr) {
         uint32_t b = bits[k];
@@ -378,6 +380,7 @@ __device__ void scan_bits(const ScanBitsArgs& a) {
     }
     uint32_t agg_c, agg_d = 0;
     const uint32_t excl_c = block_excl_scan(c, &agg_c);
+    if (a.count_slot && threadIdx.x == 0) stripe_add(a.count_slot, 0, agg_c, 0, 0, 0);
     uint32_t excl_d = 0;
     if (a.rowptr) excl_d = block_excl_scan(d, &agg_d);
     const uint32_t pc = tile_exclusive_prefix(a.flagsA, tile, a.epochA, agg_c);

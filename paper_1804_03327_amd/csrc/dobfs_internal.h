@@ -403,8 +403,11 @@ constexpr int kMbMid = 32;                      // multi-source pull: in-neighbo
 constexpr int kMbLong = kMbTileV;               // multi-source pull: rows a tile can hand to its waves
 
 struct ScanBitsArgs {
-  const uint32_t* a;         // bits = a AND NOT b_not
+  const uint32_t* a;         // bits = (a AND NOT b_not) OR b_or
   const uint32_t* b_not;     // nullable
+  const uint32_t* b_or;      // nullable
+  uint32_t* words_out;       // nullable: the bits as words (may be b_or)
+  LevelSlot* count_slot;     // nullable: the number of bits, added into the stripes' aux
   int32_t nwords, V;
   const int32_t* rowptr;     // nullable: no degrees / S / R / chunk table
   int32_t* Qout;             // the set bits as an ascending list
@@ -433,13 +436,18 @@ hipError_t launch_bfs_init(hipStream_t s, const BfsArgs& a, int32_t source, int3
                           hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 hipError_t launch_level_prep(hipStream_t s, const BfsArgs& a, int32_t level, int32_t forced_dir,
                             hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
-hipError_t launch_ctrl_init(hipStream_t s, Ctrl* ctrl, uint64_t* flags, int64_t nflags);
+// What a matvec needs cleared before it starts, in one launch: the control block's counters and
+// tickets, nflags entries of both flag arrays (0: none), nz words of z0 and of z1 (each nullable).
+hipError_t launch_mxv_init(hipStream_t s, Ctrl* ctrl, uint64_t* flagsA, uint64_t* flagsB, int64_t nflags,
+                           uint32_t* z0, uint32_t* z1, int64_t nz);
 hipError_t launch_scan_bits(hipStream_t s, const ScanBitsArgs& a);
 hipError_t launch_expand(hipStream_t s, const ExpandArgs& a, const uint32_t* m_dev,
                          const uint32_t* nf_dev);
 hipError_t launch_pull(hipStream_t s, const PullArgs& a);
-hipError_t launch_fill(hipStream_t s, uint32_t* p, int64_t n, uint32_t v);
+struct HostReport;
 hipError_t launch_s2d(hipStream_t s, const int32_t* idx, int32_t n, int32_t V, uint32_t* bits);
+// the sum of slot's aux into host->nrec, then host->seq (system-scope release): pinned host memory
+hipError_t launch_mxv_report(hipStream_t s, const LevelSlot* slot, HostReport* host, uint32_t seq);
 hipError_t launch_mxv_finalize(hipStream_t s, uint32_t* y, const uint32_t* r, int32_t nwords,
                                int32_t V, int accum, LevelSlot* slot);
 // bit v set when row v of the offsets has more than min_len entries

@@ -1599,35 +1599,41 @@ __global__ __launch_bounds__(kThreads) void k_pull(PullArgs a) {
   pull_body<EE>(a, int32_t(blockIdx.x), sh);
 }
 
-__global__ __launch_bounds__(kThreads) void k_ctrl_init(Ctrl* ctrl, uint64_t* flags,
-                                                        int64_t nflags) {
+__global__ __launch_bounds__(kThreads) void k_mxv_init(Ctrl* ctrl, uint64_t* flagsA, uint64_t* flagsB,
+                                                       int64_t nflags, uint32_t* z0, uint32_t* z1, int64_t nz) {
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
   const int64_t t0 = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  for (int64_t k = t0; k < nflags; k += stride) flags[k] = 0;
+  for (int64_t k = t0; k < nflags; k += stride) {
+    flagsA[k] = 0;
+    flagsB[k] = 0;
+  }
+  for (int64_t k = t0; k < nz; k += stride) {
+    if (z0) z0[k] = 0;
+    if (z1) z1[k] = 0;
+  }
   if (blockIdx.x == 0) {
-    for (int k = threadIdx.x; k < kSlots * kStripes; k += blockDim.x)
+    for (int k = threadIdx.x; k < 2 * kStripes; k += blockDim.x)
       zero_stripe(ctrl->slot[k / kStripes].s[k % kStripes]);
     if (threadIdx.x == 0) {
       ctrl->ticket[0] = 0;
       ctrl->ticket[1] = 0;
       ctrl->mf32 = 0;
       ctrl->nf32 = 0;
-      ctrl->src_outdeg = 0;
-      ctrl->src_indeg = 0;
-      for (int s = 0; s < kSlots; ++s) {
-        ctrl->qcount[s] = 0;
-        ctrl->mf[s] = 0;
-      }
     }
   }
 }
 
-// --------------------------------------------------------------- helpers
-__global__ __launch_bounds__(kThreads) void k_fill(uint32_t* p, int64_t n, uint32_t v) {
-  const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
+__global__ void k_mxv_report(const LevelSlot* slot, HostReport* host, uint32_t seq) {
+  const uint32_t v = threadIdx.x < kStripes ? slot->s[threadIdx.x].aux : 0u;
+  const uint32_t n = wave_sum(v);
+  if (threadIdx.x == 0) {
+    host->nrec = int32_t(n);
+    __threadfence_system();
+    __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
+// --------------------------------------------------------------- helpers
 // SPARSE2DENSE: scatter an index list into a (zeroed) bit vector.
 __global__ __launch_bounds__(kThreads) void k_s2d(const int32_t* idx, int32_t n, int32_t V,
                                                   uint32_t* bits) {
@@ -1786,9 +1792,16 @@ hipError_t launch_step_report(hipStream_t s, const Ctrl* ctrl, int32_t s_first, 
   return hipGetLastError();
 }
 
-hipError_t launch_ctrl_init(hipStream_t s, Ctrl* ctrl, uint64_t* flags, int64_t nflags) {
-  hipLaunchKernelGGL(k_ctrl_init, dim3(grid_for(nflags, kThreads, 1024)), dim3(kThreads), 0, s,
-                     ctrl, flags, nflags);
+hipError_t launch_mxv_init(hipStream_t s, Ctrl* ctrl, uint64_t* flagsA, uint64_t* flagsB, int64_t nflags,
+                           uint32_t* z0, uint32_t* z1, int64_t nz) {
+  const int64_t n = std::max(nflags, (z0 || z1) ? nz : int64_t(0));
+  hipLaunchKernelGGL(k_mxv_init, dim3(grid_for(n, kThreads * 4, 1024)), dim3(kThreads), 0, s, ctrl, flagsA, flagsB,
+                     nflags, z0, z1, (z0 || z1) ? nz : int64_t(0));
+  return hipGetLastError();
+}
+
+hipError_t launch_mxv_report(hipStream_t s, const LevelSlot* slot, HostReport* host, uint32_t seq) {
+  hipLaunchKernelGGL(k_mxv_report, dim3(1), dim3(64), 0, s, slot, host, seq);
   return hipGetLastError();
 }
 
@@ -1810,11 +1823,6 @@ hipError_t launch_pull(hipStream_t s, const PullArgs& a) {
     hipLaunchKernelGGL(k_pull<true>, dim3(g), dim3(kThreads), 0, s, a);
   else
     hipLaunchKernelGGL(k_pull<false>, dim3(g), dim3(kThreads), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill(hipStream_t s, uint32_t* p, int64_t n, uint32_t v) {
-  hipLaunchKernelGGL(k_fill, dim3(grid_for(n, kThreads * 4, 4096)), dim3(kThreads), 0, s, p, n, v);
   return hipGetLastError();
 }
 

@@ -152,3 +152,37 @@ def test_mxv_in_place_operand_reuse(cases):
                 tag = "%s dens=%g dir=%d ee=%s" % (hg.name, dens, direction, ee)
                 assert np.array_equal(got, want), tag
                 assert nnz == int(want.sum()), tag
+
+
+@pytest.mark.parametrize("V", [1, 31, 33, 255, 257, 32767, 32769, 70_001])
+def test_mxv_outputs_asked_for(V):
+    """The same result whichever outputs are asked for (the list, the count, both, neither), with
+    dirty workspaces, in place or not, at the edges of words, tiles and scan tiles."""
+    rng = np.random.default_rng(V)
+    src, dst = rng.integers(0, V, (2, 5 * V))
+    hg = gen.from_edges(V, src, dst, directed=True, name="v%d" % V)
+    g = upload(hg)
+    ws = torch.full((dobfs.mxv_workspace_bytes(g),), 0xA5, dtype=torch.uint8, device="cuda")
+    x, m, y_old = rng.random(V) < 0.2, rng.random(V) < 0.5, rng.random(V) < 0.3
+    idx = np.nonzero(x)[0].astype(np.int32)
+    for direction, acc, sparse, want_list, want_nnz, inplace in itertools.product(
+            (dobfs.DIR_PUSH, dobfs.DIR_PULL), (False, True), (False, True), (False, True), (False, True),
+            (False, True)):
+        tag = "V=%d dir=%d acc=%s sparse=%s list=%s nnz=%s inplace=%s" % (V, direction, acc, sparse, want_list,
+                                                                           want_nnz, inplace)
+        yb = _dev(pack_bits(m if inplace else y_old))
+        kw = dict(mask_bits=yb if inplace else _dev(pack_bits(m)), complement=True, direction=direction,
+                  flags=dobfs.MXV_ACCUM_OR if acc else 0, want_nnz=want_nnz, workspace=ws)
+        lst = torch.full((V,), -7, dtype=torch.int32, device="cuda") if want_list else None
+        if sparse:
+            n = dobfs.mxv(g, yb, x_idx=_dev(idx) if idx.size else None, x_nnz=idx.size, y_idx=lst, **kw)
+        else:
+            n = dobfs.mxv(g, yb, x_bits=_dev(pack_bits(x)), y_idx=lst, **kw)
+        torch.cuda.synchronize()
+        want = oracle.mxv(hg, x, m, True, acc, m if inplace else y_old).astype(bool)
+        assert np.array_equal(unpack_bits(yb.cpu().numpy(), V), want), tag
+        assert n == (int(want.sum()) if want_nnz else None), tag
+        if want_list:
+            got = lst.cpu().numpy()
+            assert np.array_equal(got[:want.sum()], np.nonzero(want)[0]) and np.all(got[want.sum():] == -7), tag
+    dobfs.graph_destroy(g)
