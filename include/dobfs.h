@@ -223,9 +223,9 @@ typedef struct {
      counts them, with their summed execution times (DOBFS_OPT_TIME_KERNELS, else 0).
      One step kernel, launched once per level, twice for a push level that needs the
      global degree scan (every multi-source push level does), once more for the step that
-     finds the end, and for any steps enqueued past the end (they exit at once); a
-     single-source launch may run several narrow push levels when no times are asked for;
-     launches_aux and ms_aux_all are 0. The sort-based push mode leaves all four at 0. */
+     finds the end, and for any steps enqueued past the end (they exit at once); when no
+     times are asked for, a launch may run several narrow push levels and counts as the
+     steps these would have taken; launches_aux and ms_aux_all are 0. The sort-based push mode leaves all four at 0. */
   int32_t launches_main;
   int32_t launches_aux;
   float ms_main_all;

@@ -561,6 +561,8 @@ struct SingleSteps {
   const BfsArgs& a;
   bool burst;  // not for timed calls (a level per launch) and the modes whose pushes need the scan
   static constexpr bool self_report = true;
+  static constexpr bool needs_records = false;
+  static constexpr int32_t push_steps = 1;  // at least
   int64_t grid() const { return main_blocks(a.nwords); }
   int64_t next_grid(const HostReport&, int32_t) const { return 0; }
   static int32_t capacity(const PersistentDevice& d) { return d.capacity; }
@@ -587,7 +589,10 @@ struct SingleSteps {
 struct BatchSteps {
   const BatchArgs& a;
   const DepthRows& rows;
+  bool burst;  // not for timed calls (a step per launch)
   static constexpr bool self_report = false;
+  static constexpr bool needs_records = true;  // next_grid reads them
+  static constexpr int32_t push_steps = 2;     // steps of a push level
   int64_t grid() const {
     return std::max<int64_t>(kExpandBlocks, std::min<int64_t>((int64_t(a.nwords) + kMbTileWords - 1) / kMbTileWords, 8192));
   }
@@ -614,11 +619,15 @@ struct BatchSteps {
     return g < grid() ? g : 0;
   }
   static int32_t capacity(const PersistentDevice& d) { return d.capacity_mb; }
-  bool narrow_first() const { return false; }
-  bool narrow_next(const HostReport&) const { return false; }
-  hipError_t step(hipStream_t s, int32_t k, int64_t blocks, bool, hipEvent_t t0, hipEvent_t t1,
-                  const StepReportArgs&) const {
-    return launch_mb_step(s, a, k, blocks, t0, t1);
+  // launches that may run several narrow levels: on graphs of low degree, as in SingleSteps
+  bool narrow_first() const { return a.low_degree != 0; }
+  bool narrow_next(const HostReport& r) const {
+    const LevelState& st = r.end;
+    return st.dir == DOBFS_DIR_PUSH && uint32_t(st.nf) <= kBurstNf * kBurstBlocks;
+  }
+  hipError_t step(hipStream_t s, int32_t k, int64_t blocks, bool narrow, hipEvent_t t0, hipEvent_t t1,
+                  const StepReportArgs& rp) const {
+    return launch_mb_step(s, a, k, blocks, burst && narrow, rp.level_end, t0, t1);
   }
   // the depth rows: a transpose that exits at once unless the state the batch's last step
   // published says the traversal is over, so the last report already finds the rows final
@@ -660,15 +669,19 @@ dobfs_status run_steps(std::atomic<int32_t>& last_steps, hipStream_t s, bool tim
     return fail(DOBFS_ERR_INVALID_ARG, "persistent grid of %d blocks (1 .. %d fit)", blocks, cap);
   if (pd) batch = next_batch = kMaxBatch;  // a launch ends with the traversal: no steps past the end
   int64_t grid = 0;  // blocks of the step launches (0: the full grid)
+  int64_t steps_alone = 1;  // steps the levels (and the end) take one per launch
   bool narrow = S.narrow_first();
   while (true) {
     if (s0 + batch > max_steps) batch = int32_t(max_steps - s0);
     const uint32_t seq = next_report_seq();
     // untimed, the batch's last step writes the report; timed, a report kernel follows the
     // steps so that every step's end event has completed when the host reads it
-    // the records are read only for the stats; without them a burst may run any number of levels
-    const int32_t rec_from = stats ? rec_first : INT32_MAX;
-    const int32_t level_end = rec_first + (stats ? kMaxRec - batch : kBurstLevels);
+    // where the records are not read a burst may run any number of levels; it leaves it to single
+    // steps to reach the level that is too deep
+    const bool records = stats || Steps::needs_records;
+    const int32_t rec_from = records ? rec_first : INT32_MAX;
+    const int32_t level_end =
+        int32_t(std::min<int64_t>(rec_first + (records ? kMaxRec - batch : kBurstLevels), max_levels - 1));
     const StepReportArgs rp{sink.dev, seq, int32_t(s0), rec_from, level_end};
     const StepReportArgs no_report{nullptr, 0u, 0, 0, level_end};
     const bool self = Steps::self_report && !timing;
@@ -715,6 +728,7 @@ dobfs_status run_steps(std::atomic<int32_t>& last_steps, hipStream_t s, bool tim
       const int32_t l = rec_first + k;
       res->sum_new += r.n_new;
       res->sum_aux += int64_t(r.aux);
+      steps_alone += r.dir == DOBFS_DIR_PUSH ? Steps::push_steps : 1;
       if (stats && l < stats->cap) {
         dobfs_level_stats& ls = stats->level[l];
         ls.dir = r.dir;
@@ -750,6 +764,8 @@ dobfs_status run_steps(std::atomic<int32_t>& last_steps, hipStream_t s, bool tim
   int32_t k_end = 0;
   while (k_end + 1 < batch && !rep->steps[k_end].done) ++k_end;
   last_steps.store(int32_t(s0) + k_end + 1, std::memory_order_relaxed);
+  // a launch that ran several levels counts as the steps they take alone
+  if (!pd) res->n_main = int32_t(std::max<int64_t>(res->n_main, steps_alone));
   return DOBFS_OK;
 }
 
@@ -1261,6 +1277,8 @@ dobfs_status dobfs::bfs_batch_rows(dobfs_graph g, const int32_t* sources, int32_
   a.alpha = double(opt.alpha);
   a.beta = double(opt.beta);
   a.edge_rule = opt.heuristic == DOBFS_HEUR_EDGES ? 1 : 0;
+  a.max_outdeg = g->max_outdeg;
+  a.low_degree = g->max_outdeg <= uint32_t(kLocalDeg) ? 1 : 0;
   a.nuniq = 0;
   for (int32_t b = 0; b < k; ++b) {
     a.src[b] = sources[b];
@@ -1290,7 +1308,7 @@ dobfs_status dobfs::bfs_batch_rows(dobfs_graph g, const int32_t* sources, int32_
     pd = persistent_device(g->device);
     if (!pd) return fail(DOBFS_ERR_UNSUPPORTED, "the persistent level loop is not available on device %d", g->device);
   }
-  st = run_steps(g->last_steps_mb, s, timing, ev, BatchSteps{a, rows}, a.ctrl, max_steps, cap,
+  st = run_steps(g->last_steps_mb, s, timing, ev, BatchSteps{a, rows, !timing}, a.ctrl, max_steps, cap,
                  cap < int64_t(g->V) + 2 ? DOBFS_ERR_UNSUPPORTED : DOBFS_ERR_INTERNAL, sink, pd, stats, &res);
   if (st != DOBFS_OK) return st;
   if (!stats) return DOBFS_OK;

@@ -98,6 +98,13 @@ __global__ __launch_bounds__(kThreads) void k_mb_init(BatchArgs a, int32_t dir0,
     for (int k = threadIdx.x; k < kSlots * kStripes; k += blockDim.x)
       zero_stripe(c->slot[k / kStripes].s[k % kStripes]);
     for (int k = threadIdx.x; k < a.nuniq; k += blockDim.x) a.Q[0][k] = a.uniq[k];
+    for (int k = threadIdx.x; k < 2 * kBurstBlocks * kMbBurstWords; k += blockDim.x)
+      (&c->burst.mb_rec[0][0][0])[k] = 0;
+    for (int k = threadIdx.x; k < 2 * kBurstBlocks; k += blockDim.x) (&c->burst.bar[0][0])[k] = 0;
+    if (threadIdx.x < kSlots) {
+      c->burst.joined[threadIdx.x][0] = 0;
+      c->burst.members[threadIdx.x][0] = 0;
+    }
     if (threadIdx.x == 0) {
       c->ticket[0] = 0;
       c->ticket[1] = 0;
@@ -109,6 +116,8 @@ __global__ __launch_bounds__(kThreads) void k_mb_init(BatchArgs a, int32_t dir0,
         c->qcount[s] = 0;
         c->mf[s] = 0;
       }
+      c->burst.head = 0;
+      c->burst.head2 = 0;
       c->bar.abort = 0;  // the persistent loop's grid barrier starts idle
       c->bar.t_end = 0;
       c->bar.gen = 0;
@@ -735,10 +744,490 @@ __device__ __forceinline__ void mb_scan_step(const BatchArgs& a, const LevelStat
   }
 }
 
+// ------------------------------------------------------------ bursts
+// Narrow push levels of a multi-source traversal, several in one launch (the single-source form and
+// how members meet are in kernels.hip and device_common.h). A level alone is two launches, a scan
+// and an expansion, 27 us on a 701 x 509 grid whatever the frontier's size. Here a member keeps the
+// vertices it lists, with their row extents and source bits, in LDS, and a level is two parts with
+// an exchange after each:
+//  - expand: an edge u -> w claims the bits of u that w lacks in w's next-frontier word; the thread
+//    that makes the word non-zero lists w. The exchange carries the totals that decide the level.
+//  - settle: the words of what was listed are complete; each goes into the visited words (and to its
+//    entry), which only its lister writes, and the next frontier's buffer is made zero.
+// The list goes through memory when a member's part outgrows the others', and at the end, where
+// what a pair of steps would leave is left: the new list, the list of the last level run (a recycled
+// buffer is cleared through it), counters and state. Everything the members share is read and
+// written by agent-scope atomics. Eight sources on a 701 x 509 grid (about 1000 levels, frontiers up
+// to 5774): 27.5 -> 9.6 ms; the chain of a level's two exchanges bounds it now.
+enum { kMbWon, kMbMnew, kMbInsub, kMbEdges, kMbPairs, kMbSpilled, kMbBitsLo, kMbBitsHi, kMbMaxdeg, kMbPart, kMbWords };
+constexpr int kMbBurstCap = 448;  // frontier vertices a member keeps in LDS
+struct MbBurstList {
+  uint64_t bits[kMbBurstCap];
+  int32_t v[kMbBurstCap], beg[kMbBurstCap], deg[kMbBurstCap];
+};
+struct MbBurstShared {
+  MbBurstList list[2];        // this member's part of the frontier, by level parity
+  int32_t off[kThreads + 1];
+  uint32_t nbuf[2];
+  uint32_t red[2][kMbBurstWords];
+  alignas(16) uint32_t tot[kMbBurstWords][kThreads / 64];
+  BurstTeam team;
+  uint32_t base;
+};
+struct MbTotals {
+  uint32_t v[kMbWords];
+};
+struct MbAcc {
+  uint32_t mnew = 0, insub = 0, edges = 0, pairs = 0, spilled = 0, maxdeg = 0;
+  uint64_t fbits = 0;
+};
+// Up to kExpandEPT edges of a thread: targets and their row extents, the bits that come along.
+struct MbEdges {
+  int32_t w[kExpandEPT], rb[kExpandEPT], re[kExpandEPT];
+  uint64_t bits[kExpandEPT];
+  int32_t n;
+};
+
+// Whether level st, of at most mf out-edges, is one for n members.
+__device__ __forceinline__ bool mb_burst_fits(const LevelState& st, uint64_t mf, uint32_t n) {
+  return !st.done && st.dir == 0 && st.phase == kPhaseScan && st.list_valid && uint32_t(st.nf) <= kBurstNf * n &&
+         mf <= uint64_t(kBurstEdges) * n;
+}
+
+__device__ __forceinline__ unsigned long long agent_load64(const uint64_t* p) {
+  return agent_load(reinterpret_cast<const unsigned long long*>(p));
+}
+__device__ __forceinline__ void agent_store64(uint64_t* p, uint64_t v) {
+  agent_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)v);
+}
+
+__device__ __forceinline__ void mb_burst_extents(const BatchArgs& a, MbEdges& x) {
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) {
+    x.rb[t] = x.re[t] = 0;
+    if (t < x.n) {
+      x.rb[t] = a.rowptr[x.w[t]];
+      x.re[t] = a.rowptr[x.w[t] + 1];
+    }
+  }
+}
+
+// The claims of level L into the frontier words Fn (all threads call), and the entries of what they
+// list. base: where the list's append counter stood when the level began.
+__device__ __forceinline__ void mb_burst_claim(const BatchArgs& a, const uint64_t* vis, uint64_t* Fn, int32_t L,
+                                               uint32_t base, int q, MbBurstShared& sh, const MbEdges& x, MbAcc& acc) {
+  uint64_t seen[kExpandEPT], old[kExpandEPT], want[kExpandEPT];
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) seen[t] = t < x.n ? agent_load64(&vis[x.w[t]]) : ~0ull;
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) {
+    want[t] = x.bits[t] & ~seen[t];
+    old[t] = ~0ull;
+    if (t < x.n && want[t])
+      old[t] = atomicOr(reinterpret_cast<unsigned long long*>(Fn + x.w[t]), (unsigned long long)want[t]);
+  }
+  uint32_t c = 0;
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) {
+    const uint64_t nb = t < x.n ? want[t] & ~old[t] : 0ull;
+    if (nb) {
+      stamp_levels(a.lvl, a.k, x.w[t], nb, L);
+      acc.pairs += uint32_t(__popcll(nb));
+      acc.fbits |= nb;
+      if (a.edge_rule && ((seen[t] | old[t] | nb) & a.active) == a.active)  // this claim completed w
+        acc.insub += uint32_t(a.colptr[x.w[t] + 1] - a.colptr[x.w[t]]);
+      if (old[t] == 0) ++c;
+    }
+  }
+  if (!__any(c != 0)) return;
+  const uint32_t incl = wave_scan_dpp(c, OpAdd{});
+  uint32_t p = 0;
+  if (lane() == 63) p = atomicAdd(&sh.nbuf[q], incl);
+  p = lane63(p) + incl - c;
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) {
+    if (t >= x.n || !want[t] || old[t] != 0) continue;
+    const uint32_t d = uint32_t(x.re[t] - x.rb[t]);
+    if (p < uint32_t(kMbBurstCap)) {
+      sh.list[q].v[p] = x.w[t];
+      sh.list[q].beg[p] = x.rb[t];
+      sh.list[q].deg[p] = int32_t(d);
+    } else {
+      const uint32_t at =
+          __hip_atomic_fetch_add(&a.ctrl->burst.head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - base;
+      agent_store(&a.Q[(L + 1) % 2][at], x.w[t]);
+      ++acc.spilled;
+    }
+    ++p;
+    acc.mnew += d;
+    acc.maxdeg = max(acc.maxdeg, d);
+  }
+}
+
+// This thread's edges when 2^shift threads take a row (burst_map_shift). The bits come later
+// (mb_burst_bits).
+__device__ __forceinline__ void mb_burst_fetch(const BatchArgs& a, const MbBurstList& l, int32_t nc, int shift,
+                                               MbEdges& x) {
+  const int32_t i = int32_t(threadIdx.x) >> shift;
+  int32_t b = 0, d = 0;
+  if (i < nc) {
+    const int32_t sub = int32_t(threadIdx.x) - (i << shift);
+    b = l.beg[i] + sub;
+    d = l.deg[i] - sub;
+  }
+  x.n = d > 0 ? min((d + (1 << shift) - 1) >> shift, kExpandEPT) : 0;
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) x.w[t] = t < x.n ? a.colind[b + (t << shift)] : 0;
+  mb_burst_extents(a, x);
+}
+__device__ __forceinline__ void mb_burst_bits(const MbBurstList& l, int shift, MbEdges& x) {
+  const uint64_t f = x.n ? l.bits[threadIdx.x >> shift] : 0ull;
+#pragma unroll
+  for (int t = 0; t < kExpandEPT; ++t) x.bits[t] = f;
+}
+
+// Expands the list's nc vertices, whatever their degrees (all threads).
+__device__ __forceinline__ void mb_burst_expand(const BatchArgs& a, const uint64_t* vis, uint64_t* Fn, int32_t L,
+                                                uint32_t base, int q, const MbBurstList& l, int32_t nc,
+                                                MbBurstShared& sh, MbAcc& acc) {
+  const int tid = threadIdx.x;
+  for (int32_t u0 = 0; u0 < nc; u0 += kThreads) {
+    const int32_t cnt = min(nc - u0, kThreads);
+    uint32_t total;
+    const uint32_t ex = block_excl_scan(tid < cnt ? uint32_t(l.deg[u0 + tid]) : 0u, &total);
+    sh.off[tid] = int32_t(ex);
+    __syncthreads();
+    for (uint32_t e0 = 0; e0 < total; e0 += kExpandChunk) {
+      MbEdges x;
+      const uint32_t e1 = e0 + uint32_t(tid);
+      x.n = e1 < total ? int32_t(min((total - e1 + kThreads - 1) / kThreads, uint32_t(kExpandEPT))) : 0;
+#pragma unroll
+      for (int t = 0; t < kExpandEPT; ++t) {
+        x.w[t] = 0;
+        x.bits[t] = 0;
+        if (t < x.n) {
+          const uint32_t e = e1 + uint32_t(t * kThreads);
+          const int32_t k = thread_search(sh.off, 0, cnt, e);
+          x.bits[t] = l.bits[u0 + k];
+          x.w[t] = a.colind[l.beg[u0 + k] + int32_t(e - uint32_t(sh.off[k]))];
+        }
+      }
+      mb_burst_extents(a, x);
+      mb_burst_claim(a, vis, Fn, L, base, q, sh, x, acc);
+    }
+    __syncthreads();  // off is free for the next vertices
+  }
+}
+
+// An exchange that carries nothing (all threads; every wave's writes before it are complete after
+// it). False: a wait gave up.
+__device__ __forceinline__ bool mb_burst_barrier(Ctrl* c, int buf, uint32_t tag, MbBurstShared& sh) {
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  const int tid = threadIdx.x;
+  if (tid == 0) agent_store(&c->burst.bar[buf][sh.team.rank], (unsigned long long)tag);
+  if (tid < sh.team.n) {
+    unsigned long long x = 0;
+    for (uint32_t k = 0; uint32_t(x) != tag && k < kBurstSpin; ++k) x = agent_load(&c->burst.bar[buf][tid]);
+    if (uint32_t(x) != tag) {
+      sh.team.ok = 0;
+      __hip_atomic_fetch_or(&c->bar.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  __syncthreads();
+  return sh.team.ok != 0;
+}
+
+// Waits for every member's words with this tag and combines them (all threads; ends past a
+// barrier). False: a wait gave up.
+__device__ __forceinline__ bool mb_burst_gather(Ctrl* c, int buf, uint32_t tag, MbBurstShared& sh, MbTotals* out) {
+  static_assert(kMbBurstWords == 16 && kBurstBlocks * kMbBurstWords == 2 * kThreads, "two words a thread");
+  const int tid = threadIdx.x;
+  const int word = tid & 15;
+  auto join = [&](uint32_t p, uint32_t o) {
+    return word >= kMbMaxdeg ? max(p, o) : (word >= kMbBitsLo ? p | o : p + o);
+  };
+  uint32_t v = 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int m = (tid >> 4) + h * (kBurstBlocks / 2);
+    if (m < sh.team.n && word < kMbWords) {
+      unsigned long long x = agent_load(&c->burst.mb_rec[buf][m][word]);
+      for (uint32_t k = 0; uint32_t(x >> 32) != tag && k < kBurstSpin; ++k)
+        x = agent_load(&c->burst.mb_rec[buf][m][word]);
+      if (uint32_t(x >> 32) != tag) {
+        sh.team.ok = 0;
+        __hip_atomic_fetch_or(&c->bar.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      v = join(v, uint32_t(x));
+    }
+  }
+#pragma unroll
+  for (int d = 16; d < 64; d *= 2) v = join(v, uint32_t(__shfl_xor(int(v), d, 64)));
+  if (lane() < kMbBurstWords) sh.tot[lane()][tid >> 6] = v;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kMbWords; ++k) {
+    const uint4 t = *reinterpret_cast<const uint4*>(&sh.tot[k][0]);
+    const uint32_t r = k >= kMbMaxdeg ? max(max(t.x, t.y), max(t.z, t.w))
+                                      : (k >= kMbBitsLo ? (t.x | t.y | t.z | t.w) : t.x + t.y + t.z + t.w);
+    out->v[k] = __builtin_amdgcn_readfirstlane(r);
+  }
+  return sh.team.ok != 0;
+}
+
+// The state entering the level after st, given st's totals (next_state for a listing push).
+__device__ __forceinline__ LevelState mb_burst_next(const BatchArgs& a, int32_t forced, const LevelState& st,
+                                                    const MbTotals& t) {
+  LevelState next = st;
+  next.level = st.level + 1;
+  if (t.v[kMbWon] == 0) {
+    next.done = 1;
+    next.levels = next.level;
+    return next;
+  }
+  next.m_u = st.m_u - (a.edge_rule ? int64_t(t.v[kMbInsub]) : 0);
+  next.dir = next_direction_rule(a.heuristic, a.alpha, a.beta, 0, a.V, st.nf, int64_t(t.v[kMbWon]),
+                                 int64_t(t.v[kMbMnew]), next.m_u);
+  if (a.mode == 1) next.dir = 0;  // push only
+  if (a.mode == 5) next.dir = 1;  // pull only
+  if (forced >= 0) next.dir = forced;
+  next.nf = int32_t(t.v[kMbWon]);
+  next.list_valid = 1;
+  next.active = uint64_t(t.v[kMbBitsLo]) | (uint64_t(t.v[kMbBitsHi]) << 32);
+  next.local = 0;
+  next.phase = next.dir == 0 ? kPhaseScan : kPhaseWhole;
+  return next;
+}
+
+// Entries [lo, hi) of level L's list in memory into the visited words (which may lack them).
+__device__ __forceinline__ void mb_burst_settle(uint64_t* vis, const uint64_t* F, const int32_t* Q, uint32_t lo,
+                                                uint32_t hi) {
+  for (uint32_t i = lo + threadIdx.x; i < hi; i += kThreads) {
+    const int32_t v = agent_load(&Q[i]);
+    const uint64_t f = agent_load64(&F[v]), m = agent_load64(&vis[v]);
+    agent_store64(&vis[v], m | f);
+  }
+}
+// This member's share of zeroing a whole frontier buffer.
+__device__ __forceinline__ void mb_burst_zero(const BatchArgs& a, uint64_t* F, uint32_t r, uint32_t n) {
+  for (int64_t i = int64_t(r) * kThreads + threadIdx.x; i < a.V; i += int64_t(n) * kThreads) agent_store64(&F[i], 0ull);
+}
+
+// Step s from its level st on (candidate blocks; prev: the state of the level before): levels while
+// they fit and stay below level_end. Block 0 leaves what the two steps of the last of them would
+// leave, or, when the traversal ended, the final state.
+__device__ __forceinline__ void mb_burst_run(const BatchArgs& a, LevelState st, const LevelState& prev, int32_t s,
+                                             int32_t level_end, MbBurstShared& sh) {
+  Ctrl* c = a.ctrl;
+  const int tid = threadIdx.x;
+  for (int i = tid; i < 2 * kMbBurstWords; i += kThreads) (&sh.red[0][0])[i] = 0;
+  if (tid < 2) sh.nbuf[tid] = 0;
+  if (!burst_join(c, s, kBurstBlocks, sh.team)) return;
+  const uint32_t n = uint32_t(sh.team.n), r = uint32_t(sh.team.rank);
+  uint64_t* vis = a.vis[st.vis_idx];
+  uint32_t base = sh.team.head;
+  int buf = 0, bbuf = 0;
+  int32_t nc = 0;        // vertices of this level in the list of its parity
+  bool listed = true;    // the frontier is in memory (else in the members' lists)
+  bool fetched = false;  // x holds this level's edges, 2^shift threads a row
+  int shift = 0;
+  uint32_t m_f = 0;      // out-edges of a frontier kept in the lists
+  MbEdges x;
+  auto share = [&](uint32_t nf, uint32_t* lo, uint32_t* hi) {
+    const uint32_t per = (nf + n - 1) / n;
+    *lo = min(r * per, nf);
+    *hi = min(*lo + per, nf);
+  };
+  bool ok = true;
+  {  // what the first level's scan step would do: merge, and make the next frontier's buffer zero
+    const int32_t L = st.level;
+    uint32_t lo, hi;
+    share(uint32_t(st.nf), &lo, &hi);
+    if (L >= 1) {
+      mb_burst_settle(vis, mb_frontier(a, L), a.Q[L % 2], lo, hi);
+      uint64_t* Fn = mb_frontier(a, L + 1);
+      if (mb_frontier_recycled(L + 1) && (prev.list_valid || prev.dir == 0)) {
+        share(uint32_t(prev.nf), &lo, &hi);
+        for (uint32_t i = lo + tid; i < hi; i += kThreads) agent_store64(&Fn[agent_load(&a.Q[(L + 1) % 2][i])], 0ull);
+      } else {
+        mb_burst_zero(a, Fn, r, n);
+      }
+    }
+    ok = mb_burst_barrier(c, bbuf, 2u * uint32_t(L) + 1u, sh);
+    bbuf ^= 1;
+  }
+  while (ok) {
+    const int32_t L = st.level;
+    const int p = L & 1, q = p ^ 1;
+    uint64_t* Fn = mb_frontier(a, L + 1);
+    MbAcc acc;
+    uint32_t lo = 0, hi = 0;
+    if (listed) {  // this member's part of the list in memory, kMbBurstCap vertices at a time
+      share(uint32_t(st.nf), &lo, &hi);
+      const uint64_t* Fc = mb_frontier(a, L);
+      for (uint32_t i0 = lo; i0 < hi; i0 += kMbBurstCap) {
+        nc = int32_t(min(hi - i0, uint32_t(kMbBurstCap)));
+        for (int32_t i = tid; i < nc; i += kThreads) {
+          const int32_t u = agent_load(&a.Q[p][i0 + uint32_t(i)]);
+          const int32_t b = a.rowptr[u], d = a.rowptr[u + 1] - b;
+          sh.list[p].v[i] = u;
+          sh.list[p].beg[i] = b;
+          sh.list[p].deg[i] = d;
+          sh.list[p].bits[i] = agent_load64(&Fc[u]);
+          acc.edges += uint32_t(d);
+        }
+        __syncthreads();
+        mb_burst_expand(a, vis, Fn, L, base, q, sh.list[p], nc, sh, acc);
+        __syncthreads();
+      }
+    } else if (fetched) {
+      mb_burst_bits(sh.list[p], shift, x);
+      mb_burst_claim(a, vis, Fn, L, base, q, sh, x, acc);
+    } else {
+      mb_burst_expand(a, vis, Fn, L, base, q, sh.list[p], nc, sh, acc);
+    }
+    // this block's totals (the vertices found are counted in nbuf)
+    {
+      auto add = [&](int k, uint32_t v) {
+        v = wave_sum(v);
+        if (lane() == 0 && v) atomicAdd(&sh.red[p][k], v);
+      };
+      if (__any(acc.pairs != 0)) {
+        add(kMbMnew, acc.mnew);
+        add(kMbPairs, acc.pairs);
+        if (a.edge_rule) add(kMbInsub, acc.insub);
+        const uint32_t v = wave_max32(acc.maxdeg);
+        const uint64_t f = wave_or64(acc.fbits);
+        if (lane() == 0) {
+          atomicMax(&sh.red[p][kMbMaxdeg], v);
+          atomicOr(&sh.red[p][kMbBitsLo], uint32_t(f));
+          atomicOr(&sh.red[p][kMbBitsHi], uint32_t(f >> 32));
+        }
+      }
+      if (listed) add(kMbEdges, acc.edges);
+      if (__any(acc.spilled != 0)) add(kMbSpilled, acc.spilled);
+    }
+    __syncthreads();  // the totals stand, and every claim has returned
+    if (tid == 64) sh.nbuf[p] = 0;  // last read a level ago, next counted in at the next level
+    const uint32_t tag = uint32_t(L) + 1u;
+    const uint32_t found = sh.nbuf[q];
+    const int32_t nc_next = int32_t(min(found, uint32_t(kMbBurstCap)));
+    if (tid < kMbWords) {
+      uint32_t v = sh.red[p][tid];
+      if (tid == kMbWon) v = found;
+      if (tid == kMbPart) v = burst_part(found, sh.red[p][kMbMnew]);
+      agent_store(&c->burst.mb_rec[buf][r][tid], ((unsigned long long)tag << 32) | v);
+    }
+    // what the next level can do before the others are through
+    shift = burst_map_shift(sh.red[p][kMbMaxdeg], nc_next);
+    fetched = shift >= 0;
+    if (fetched) mb_burst_fetch(a, sh.list[q], nc_next, shift, x);
+    MbTotals t;
+    ok = mb_burst_gather(c, buf, tag, sh, &t);
+    if (!ok) break;
+    buf ^= 1;
+    if (tid < kMbBurstWords) sh.red[p][tid] = 0;  // next used two levels on
+    if (!listed) t.v[kMbEdges] = m_f;
+    m_f = t.v[kMbMnew];
+    const int32_t forced = L + 1 < a.n_forced ? int32_t(c->forced[L + 1]) : -1;
+    const LevelState next = mb_burst_next(a, forced, st, t);
+    const bool go_on = mb_burst_fits(next, t.v[kMbMnew], n) && L + 1 < level_end;
+    if (r == 0 && tid == 0) {
+      if (go_on || next.done) {
+        LevelRecord rec;
+        rec.dir = st.dir;
+        rec.nf = st.nf;
+        rec.n_new = int32_t(t.v[kMbWon]);
+        rec.variant = 0;
+        rec.edges = rec.m_f = int64_t(t.v[kMbEdges]);
+        rec.mnew = t.v[kMbMnew];
+        rec.insub = t.v[kMbInsub];
+        rec.aux = t.v[kMbPairs];
+        c->rec[L % kRing] = rec;
+      }
+      if (!go_on) {
+        if (next.done) {
+          c->ring[s % kRing] = next;
+        } else {
+          LevelState last = st;
+          last.phase = kPhaseExpand;  // the level has been run
+          c->ring[s % kRing] = last;
+        }
+        Stripe& z = c->slot[s % kSlots].s[0];
+        z.count = t.v[kMbWon];
+        z.aux = t.v[kMbPairs];
+        z.edges = t.v[kMbEdges];
+        z.mnew = t.v[kMbMnew];
+        z.insub = t.v[kMbInsub];
+        z.fbits = uint64_t(t.v[kMbBitsLo]) | (uint64_t(t.v[kMbBitsHi]) << 32);
+        c->mf[s % kSlots] = t.v[kMbEdges];
+      }
+    }
+    if (next.done) break;
+    const bool relist = t.v[kMbSpilled] != 0 ||
+                        (t.v[kMbPart] > kBurstEven && t.v[kMbPart] * n * 2u > 3u * burst_part(t.v[kMbWon], t.v[kMbMnew]));
+    if (relist || !go_on) {  // the next frontier's list
+      if (tid == 0 && nc_next)
+        sh.base = __hip_atomic_fetch_add(&c->burst.head, uint32_t(nc_next), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - base;
+      __syncthreads();
+      for (int32_t i = tid; i < nc_next; i += kThreads)
+        agent_store(&a.Q[q][sh.base + uint32_t(i)], sh.list[q].v[i]);
+    }
+    if (!go_on) {
+      if (!listed) {  // and this level's, through which its buffer may be cleared
+        __syncthreads();
+        if (tid == 0 && nc)
+          sh.base = __hip_atomic_fetch_add(&c->burst.head2, uint32_t(nc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        for (int32_t i = tid; i < nc; i += kThreads) agent_store(&a.Q[p][sh.base + uint32_t(i)], sh.list[p].v[i]);
+      }
+      break;
+    }
+    // settle: this level's buffer is the one after the next where the buffers alternate
+    if (mb_frontier_recycled(L + 2)) {
+      uint64_t* Fc = mb_frontier(a, L);
+      if (listed) {
+        for (uint32_t i = lo + tid; i < hi; i += kThreads) agent_store64(&Fc[agent_load(&a.Q[p][i])], 0ull);
+      } else {
+        for (int32_t i = tid; i < nc; i += kThreads) agent_store64(&Fc[sh.list[p].v[i]], 0ull);
+      }
+    } else {
+      mb_burst_zero(a, mb_frontier(a, L + 2), r, n);
+    }
+    if (relist) {
+      ok = mb_burst_barrier(c, bbuf, 2u * uint32_t(L) + 2u, sh);
+      bbuf ^= 1;
+      if (!ok) break;
+      share(t.v[kMbWon], &lo, &hi);
+      mb_burst_settle(vis, Fn, a.Q[q], lo, hi);
+      base += t.v[kMbWon];
+    } else {
+      for (int32_t i = tid; i < nc_next; i += kThreads) {
+        const int32_t v = sh.list[q].v[i];
+        const uint64_t f = agent_load64(&Fn[v]), m = agent_load64(&vis[v]);
+        agent_store64(&vis[v], m | f);
+        sh.list[q].bits[i] = f;
+      }
+    }
+    ok = mb_burst_barrier(c, bbuf, 2u * uint32_t(L) + 3u, sh);
+    bbuf ^= 1;
+    st = next;
+    nc = nc_next;
+    listed = relist;
+  }
+  if (!ok && r == 0 && tid == 0) {  // nothing may go on from here; the report says why
+    st.done = 1;
+    st.levels = st.level;
+    c->ring[s % kRing] = st;
+  }
+}
+
 union MbShared {
   MbExpandShared e;
   MbPullShared p;
   MbSparseShared f;
+  MbBurstShared b;
 };
 
 // The work of step s (state st, prev: the state before it) over the launch's grid.
@@ -766,7 +1255,10 @@ __device__ __forceinline__ void mb_step_body(const BatchArgs& a, const LevelStat
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_mb_step(BatchArgs a, int32_t s) {
+// kBurst: the form that may run several narrow levels, launched where they are expected
+// (BatchSteps); either form is right for any level.
+template <bool kBurst>
+__global__ __launch_bounds__(kThreads) void k_mb_step(BatchArgs a, int32_t s, int32_t level_end) {
   __shared__ MbShared sh;
   LevelTotals tot;
   LevelState prev;
@@ -774,6 +1266,13 @@ __global__ __launch_bounds__(kThreads) void k_mb_step(BatchArgs a, int32_t s) {
   const LevelState st = mb_step_state(a, s, &tot, &prev, &new_level);
   if (blockIdx.x == 0) publish_step(a.ctrl, s, st, prev, tot, new_level);
   if (st.done) return;
+  if (kBurst) {
+    const uint64_t bound = s > 0 && a.edge_rule ? tot.mnew : uint64_t(st.nf) * a.max_outdeg;
+    if (mb_burst_fits(st, bound, kBurstBlocks)) {
+      if (blockIdx.x % 8 == 0 && blockIdx.x < 8 * kBurstBlocks) mb_burst_run(a, st, prev, s, level_end, sh.b);
+      return;
+    }
+  }
   mb_step_body(a, st, prev, s, sh);
 }
 
@@ -940,12 +1439,13 @@ hipError_t launch_mb_init(hipStream_t s, const BatchArgs& a, int32_t dir0, int64
 
 // By default a block per pull tile, at most 8192: every block of every step derives the step's
 // state first, which on graphs of millions of vertices costs more than a second tile per block.
-hipError_t launch_mb_step(hipStream_t s, const BatchArgs& a, int32_t step, int64_t blocks, hipEvent_t t0,
-                          hipEvent_t t1) {
+hipError_t launch_mb_step(hipStream_t s, const BatchArgs& a, int32_t step, int64_t blocks, bool burst,
+                          int32_t level_end, hipEvent_t t0, hipEvent_t t1) {
   const int64_t tiles = (int64_t(a.nwords) + kMbTileWords - 1) / kMbTileWords;
   const int64_t full = std::max<int64_t>(kExpandBlocks, std::min<int64_t>(tiles, 8192));
   const dim3 g(unsigned(blocks > 0 && blocks < full ? blocks : full));
-  return launch_k(k_mb_step, g, s, t0, t1, a, step);
+  if (burst) return launch_k(k_mb_step<true>, g, s, t0, t1, a, step, level_end);
+  return launch_k(k_mb_step<false>, g, s, t0, t1, a, step, level_end);
 }
 
 hipError_t launch_mb_steps(hipStream_t s, const BatchArgs& a, int32_t s_first, int32_t n, int32_t blocks,

@@ -693,5 +693,83 @@ __device__ __forceinline__ bool grid_barrier(GridBar* bar, uint32_t target, uint
   return s_ok != 0;
 }
 
+// ------------------------------------------------- bursts: what both kinds share
+constexpr uint32_t kBurstEdges = 1024;       // most out-edges of a burst level, per member
+constexpr uint32_t kBurstEven = 64;          // parts up to this size are not evened out (256: grid levels 15% slower)
+constexpr uint32_t kBurstJoinPolls = 16;     // the leader's wait for the candidates (about 4 us)
+constexpr uint32_t kBurstSpin = 1u << 22;    // bound of every other wait (polls)
+
+// Who takes part in a burst, in LDS: how many members, this block's place among them (-1: none),
+// whether every wait has ended well, and where the list's append counter stood.
+struct BurstTeam {
+  int32_t n, rank, ok;
+  uint32_t head;
+};
+
+__device__ __forceinline__ uint32_t agent_load(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int32_t agent_load(const int32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long agent_load(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ void agent_store(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The size of a part of a frontier, in threads of kExpandEPT edges: what a member's rounds go by.
+__device__ __forceinline__ uint32_t burst_part(uint32_t vertices, uint32_t edges) {
+  return max(vertices, edges / uint32_t(kExpandEPT));
+}
+
+// (Two threads a row whatever the room: 13.6 instead of 11.6 ms on the 2048 x 2048 grid.)
+// Rows of at most maxdeg entries take 2^shift threads each, entries sub, sub + 2^shift, .. for the
+// sub-th: as many as nc rows leave room for in the block, so that a thread has few edges in a row.
+// -1 where a thread would have more than kExpandEPT.
+__device__ __forceinline__ int burst_map_shift(uint32_t maxdeg, int32_t nc) {
+  int shift = nc <= kThreads / 8 ? 3 : nc <= kThreads / 4 ? 2 : nc <= kThreads / 2 ? 1 : 0;
+  return nc <= kThreads && maxdeg <= (uint32_t(kExpandEPT) << shift) ? shift : -1;
+}
+
+// Joins step s's burst, one for `most` members (all threads of a candidate block). False: too late.
+__device__ __forceinline__ bool burst_join(Ctrl* c, int32_t s, uint32_t most, BurstTeam& t) {
+  if (threadIdx.x == 0) {
+    BurstCtl& b = c->burst;
+    uint32_t* joined = &b.joined[s % kSlots][0];
+    unsigned long long* members = &b.members[s % kSlots][0];
+    t.rank = -1;
+    t.ok = 1;
+    if (most == 1) {
+      t.n = 1;
+      t.rank = 0;
+      t.head = agent_load(&b.head);
+    } else if (blockIdx.x == 0) {
+      for (uint32_t p = 0; p < kBurstJoinPolls && agent_load(joined) < uint32_t(kBurstBlocks - 1); ++p) {}
+      const uint32_t got = __hip_atomic_fetch_or(joined, kBurstClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      t.n = int32_t(min(got, uint32_t(kBurstBlocks - 1))) + 1;
+      t.rank = 0;
+      t.head = agent_load(&b.head);
+      agent_store(&b.head2, 0u);
+      __builtin_amdgcn_s_waitcnt(0);
+      agent_store(members, (unsigned long long)uint32_t(t.n) | ((unsigned long long)t.head << 32));
+    } else {
+      const uint32_t at = __hip_atomic_fetch_add(joined, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!(at & kBurstClosed)) {
+        unsigned long long m = 0;
+        for (uint32_t p = 0; p < kBurstSpin && m == 0; ++p) m = agent_load(members);
+        t.n = int32_t(uint32_t(m));
+        t.head = uint32_t(m >> 32);
+        t.rank = m ? int32_t(at) + 1 : -1;
+        if (!m) __hip_atomic_fetch_or(&c->bar.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+  }
+  __syncthreads();
+  return t.rank >= 0;
+}
+
 }  // namespace
 }  // namespace dobfs

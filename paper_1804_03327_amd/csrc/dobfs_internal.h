@@ -96,13 +96,19 @@ struct GridBar {
 // half, and wait for everybody's: the exchange of the totals is the barrier.
 constexpr int kBurstBlocks = 32;      // members at most: about one per CU of an XCD
 constexpr int kBurstWords = 8;
-constexpr uint32_t kBurstNf = 128;    // most frontier vertices of a burst level, per member
+constexpr int kMbBurstWords = 16;
+constexpr uint32_t kBurstNf = 256;    // most frontier vertices of a burst level, per member
 constexpr uint32_t kBurstDeg = 1024;  // largest out-degree (a row is one member's)
 struct BurstCtl {
   alignas(128) uint32_t joined[kSlots][32];          // a line per slot; kBurstClosed: too late
   alignas(128) unsigned long long members[kSlots][16];  // members | head << 32; 0: not yet known
   alignas(128) uint32_t head;
   alignas(128) unsigned long long rec[2][kBurstBlocks][kBurstWords];
+  // multi-source bursts: the counter of a second list, appended to once a burst; a longer record;
+  // and the tags of the exchanges that carry nothing
+  alignas(128) uint32_t head2;
+  alignas(128) unsigned long long mb_rec[2][kBurstBlocks][kMbBurstWords];
+  alignas(128) unsigned long long bar[2][kBurstBlocks];
 };
 constexpr uint32_t kBurstClosed = 1u << 31;
 
@@ -374,7 +380,8 @@ struct BatchArgs {
   int32_t edge_rule;
   int32_t local_push;        // always 0: the multi-source push always scans
   int32_t n_forced;          // levels whose direction Ctrl::forced fixes
-  int32_t low_degree;        // unused here
+  int32_t low_degree;        // every out-degree of the graph is <= kLocalDeg
+  uint32_t max_outdeg;       // largest out-degree of the graph
   Sched sched;               // unused here (no local push)
   int32_t src[kMaxSources];  // source of bit b
   int32_t uniq[kMaxSources]; // the distinct sources: the first frontier list
@@ -498,8 +505,9 @@ hipError_t launch_mb_init(hipStream_t s, const BatchArgs& a, int32_t dir0, int64
                          hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 // Step `step` of the multi-source step loop (k_mb_step) on `blocks` blocks (0 or more than
 // the full grid: the full grid).
-hipError_t launch_mb_step(hipStream_t s, const BatchArgs& a, int32_t step, int64_t blocks = 0,
-                          hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
+// burst: the form that may run several narrow levels, all below level_end.
+hipError_t launch_mb_step(hipStream_t s, const BatchArgs& a, int32_t step, int64_t blocks, bool burst,
+                          int32_t level_end, hipEvent_t t0, hipEvent_t t1);
 // The persistent form of the multi-source step loop (k_mb_steps): steps s_first .. s_first +
 // n - 1 in one launch of `blocks` co-resident blocks, a grid barrier between steps; the report
 // is written afterwards by launch_step_report.

@@ -1037,16 +1037,12 @@ __device__ __forceinline__ void step_body(const BfsArgs& a, const LevelState& st
 // and a member publishes its totals only after what the others may read has completed. The visited
 // word an edge looks at before its claim may be stale; a stale word costs a claim that fails.
 //
-// Measured on 2048 x 2048 grids (2700 levels, frontiers up to 2758): 34.5 -> 13.6 ms per search
-// (12.5 -> 5.0 us per level); a tree of 750 000 vertices 505 -> 432 us. A burst level is bound by
-// its chain: neighbours, then visited words and row extents (0.9 us each when they miss the L2),
-// claims, totals. The limits are one round of a member's threads: a wider level would take it two,
-// and the whole chip runs levels of some ten thousand edges as fast.
-constexpr uint32_t kBurstEdges = 1024;       // most out-edges of a burst level, per member
+// Measured on 2048 x 2048 grids (2700 levels, frontiers up to 2758): 34.4 -> 11.6 ms per search
+// (12.5 -> 4.3 us per level); a tree of 750 000 vertices 505 -> 432 us. A burst level is bound by
+// its chain: neighbours, then visited words and row extents (0.8 us each when they miss the L2),
+// claims, totals. The limits (kBurstNf, kBurstEdges) are one round of a member's threads: a wider
+// level would take it two, and the whole chip runs levels of some ten thousand edges as fast.
 constexpr int kBurstCap = 512;               // frontier vertices a member keeps in LDS
-constexpr uint32_t kBurstJoinPolls = 16;     // the leader's wait for the candidates (about 4 us)
-constexpr uint32_t kBurstSpin = 1u << 22;    // bound of every other wait (polls)
-constexpr int kBurstMapDeg = 2 * kExpandEPT; // rows of up to this many entries: two threads a vertex
 static_assert(kBurstBlocks * kBurstWords == kThreads, "a thread per exchanged word");
 
 struct BurstList {
@@ -1058,23 +1054,9 @@ struct BurstShared {
   uint32_t nbuf[2];                       // vertices found (kept in list or past it in memory)
   uint32_t red[2][kBurstWords];           // this block's totals
   alignas(16) uint32_t tot[kBurstWords][kThreads / 64];
-  int32_t n, rank, ok;
-  uint32_t head, base;
+  BurstTeam team;
+  uint32_t base;
 };
-
-__device__ __forceinline__ uint32_t agent_load(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ int32_t agent_load(const int32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long agent_load(const unsigned long long* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <class T>
-__device__ __forceinline__ void agent_store(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // The totals of a burst level: vertices found, their out-edges and in-edges, edges read, vertices
 // past the LDS lists; largest: out-degree, size of one member's part.
@@ -1089,51 +1071,9 @@ __device__ __forceinline__ bool burst_fits(const LevelState& st, uint32_t mf, ui
          mf <= kBurstEdges * n && maxdeg <= kBurstDeg;
 }
 
-// The size of a part of a frontier, in vertices of kBurstMapDeg edges: what a member's rounds go by.
-__device__ __forceinline__ uint32_t burst_part(uint32_t vertices, uint32_t edges) {
-  return max(vertices, edges / uint32_t(kBurstMapDeg));
-}
-
 // How many members a burst on this graph is for. Where there are hubs a search is narrow for a
 // level or two and then wide at once: the leader runs those alone, and nobody has to join.
 __device__ __forceinline__ uint32_t burst_members(const BfsArgs& a) { return a.low_degree ? kBurstBlocks : 1; }
-
-// Joins step s's burst, one for `most` members (all threads of a candidate block). False: too late.
-__device__ __forceinline__ bool burst_join(Ctrl* c, int32_t s, uint32_t most, BurstShared& sh) {
-  if (threadIdx.x == 0) {
-    BurstCtl& b = c->burst;
-    uint32_t* joined = &b.joined[s % kSlots][0];
-    unsigned long long* members = &b.members[s % kSlots][0];
-    sh.rank = -1;
-    sh.ok = 1;
-    if (most == 1) {
-      sh.n = 1;
-      sh.rank = 0;
-      sh.head = agent_load(&b.head);
-    } else if (blockIdx.x == 0) {
-      for (uint32_t p = 0; p < kBurstJoinPolls && agent_load(joined) < uint32_t(kBurstBlocks - 1); ++p) {}
-      const uint32_t got = __hip_atomic_fetch_or(joined, kBurstClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      sh.n = int32_t(min(got, uint32_t(kBurstBlocks - 1))) + 1;
-      sh.rank = 0;
-      sh.head = agent_load(&b.head);
-      agent_store(members, (unsigned long long)uint32_t(sh.n) | ((unsigned long long)sh.head << 32));
-    } else {
-      const uint32_t t = __hip_atomic_fetch_add(joined, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (!(t & kBurstClosed)) {
-        unsigned long long m = 0;
-        for (uint32_t p = 0; p < kBurstSpin && m == 0; ++p) m = agent_load(members);
-        sh.n = int32_t(uint32_t(m));
-        sh.head = uint32_t(m >> 32);
-        sh.rank = m ? int32_t(t) + 1 : -1;
-        if (!m) __hip_atomic_fetch_or(&c->bar.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-    }
-  }
-  if (threadIdx.x < 2 * kBurstWords) (&sh.red[0][0])[threadIdx.x] = 0;
-  if (threadIdx.x < 2) sh.nbuf[threadIdx.x] = 0;
-  __syncthreads();
-  return sh.rank >= 0;
-}
 
 // Up to kExpandEPT edges a thread works on at once: targets, sources, and the targets' visited
 // words and row extents.
@@ -1203,23 +1143,22 @@ __device__ __forceinline__ void burst_look(const BfsArgs& a, const uint32_t* cla
   }
 }
 
-// The kExpandEPT edges of this thread when each of the list's nc vertices (at most kThreads / 2)
-// has at most kBurstMapDeg: two threads a vertex.
+// The kExpandEPT edges of this thread when 2^shift threads take a row (burst_map_shift).
 __device__ __forceinline__ void burst_fetch_map(const BfsArgs& a, const uint32_t* claim, const BurstList& l, int32_t nc,
-                                                BurstEdges& x) {
-  const int32_t i = int32_t(threadIdx.x) >> 1;
+                                                int shift, BurstEdges& x) {
+  const int32_t i = int32_t(threadIdx.x) >> shift;
   int32_t b = 0, d = 0, u = 0;
   if (i < nc) {
-    const int32_t e0 = (int32_t(threadIdx.x) & 1) * kExpandEPT;
+    const int32_t sub = int32_t(threadIdx.x) - (i << shift);
     u = l.v[i];
-    b = l.beg[i] + e0;
-    d = l.deg[i] - e0;
+    b = l.beg[i] + sub;
+    d = l.deg[i] - sub;
   }
-  x.n = min(max(d, 0), kExpandEPT);
+  x.n = d > 0 ? min((d + (1 << shift) - 1) >> shift, kExpandEPT) : 0;
 #pragma unroll
   for (int t = 0; t < kExpandEPT; ++t) {
     x.u[t] = u;
-    x.w[t] = t < x.n ? a.colind[b + t] : 0;
+    x.w[t] = t < x.n ? a.colind[b + (t << shift)] : 0;
   }
   burst_look(a, claim, x);
 }
@@ -1280,10 +1219,10 @@ __device__ __forceinline__ bool burst_gather(Ctrl* c, int buf, uint32_t tag, uns
   const int tid = threadIdx.x;
   const int m = tid >> 3, word = tid & 7;
   uint32_t v = 0;
-  if (m < sh.n && word < kTotWords) {
+  if (m < sh.team.n && word < kTotWords) {
     for (uint32_t k = 0; uint32_t(x >> 32) != tag && k < kBurstSpin; ++k) x = agent_load(burst_word(c, buf));
     if (uint32_t(x >> 32) != tag) {
-      sh.ok = 0;
+      sh.team.ok = 0;
       __hip_atomic_fetch_or(&c->bar.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     v = uint32_t(x);
@@ -1301,7 +1240,7 @@ __device__ __forceinline__ bool burst_gather(Ctrl* c, int buf, uint32_t tag, uns
     const uint32_t r = k >= kTotMaxdeg ? max(max(t.x, t.y), max(t.z, t.w)) : t.x + t.y + t.z + t.w;
     out->v[k] = __builtin_amdgcn_readfirstlane(r);
   }
-  return sh.ok != 0;
+  return sh.team.ok != 0;
 }
 
 // The state entering the level after st, given st's totals: what next_state makes of them for a
@@ -1342,11 +1281,13 @@ __device__ __forceinline__ LevelState burst_next(const BfsArgs& a, int32_t force
 __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32_t s, const StepReportArgs& rp,
                                           BurstShared& sh) {
   Ctrl* c = a.ctrl;
-  if (!burst_join(c, s, burst_members(a), sh)) return;
+  if (threadIdx.x < 2 * kBurstWords) (&sh.red[0][0])[threadIdx.x] = 0;
+  if (threadIdx.x < 2) sh.nbuf[threadIdx.x] = 0;
+  if (!burst_join(c, s, burst_members(a), sh.team)) return;
   const int tid = threadIdx.x;
-  const uint32_t n = uint32_t(sh.n), r = uint32_t(sh.rank);
+  const uint32_t n = uint32_t(sh.team.n), r = uint32_t(sh.team.rank);
   uint32_t* claim = a.vis[st.vis_idx];
-  uint32_t base = sh.head;
+  uint32_t base = sh.team.head;
   int buf = 0;
   int32_t nc = 0;            // vertices of this level in the list of its parity
   bool listed = true;        // the frontier is in memory (else in the members' lists)
@@ -1412,8 +1353,9 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
     if (n > 1) word = agent_load(burst_word(c, buf));
     nc = int32_t(min(found, uint32_t(kBurstCap)));
     // what the next level can do before the others are through
-    fetched = sh.red[p][kTotMaxdeg] <= uint32_t(kBurstMapDeg) && nc <= kThreads / 2;
-    if (fetched) burst_fetch_map(a, claim, sh.list[q], nc, x);
+    const int shift = burst_map_shift(sh.red[p][kTotMaxdeg], nc);
+    fetched = shift >= 0;
+    if (fetched) burst_fetch_map(a, claim, sh.list[q], nc, shift, x);
     BurstTotals t;
     if (!burst_gather(c, buf, tag, word, sh, &t)) {
       failed = true;
@@ -1448,7 +1390,7 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
     // shared out anew when a list overflowed, or when one member's part takes more than one round
     // of its threads and is half again the average
     listed = t.v[kTotSpilled] != 0 ||
-             (t.v[kTotPart] > kBurstNf && t.v[kTotPart] * n * 2u > 3u * burst_part(t.v[kTotWon], t.v[kTotMnew]));
+             (t.v[kTotPart] > kBurstEven && t.v[kTotPart] * n * 2u > 3u * burst_part(t.v[kTotWon], t.v[kTotMnew]));
     if (!next.done && (listed || !go_on)) burst_flush(a, L, base, sh.list[q], nc, sh);
     if (!go_on) {
       if (next.done) st = next;

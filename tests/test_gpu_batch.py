@@ -383,3 +383,57 @@ def test_batch_pull_after_short_list(leaves):
                 d, st = _run(g, srcs, dobfs.make_options("full", heur, 0.01, 0.01, forced_dirs=sc))
                 _check(hg, srcs, d, st, tag)
     dobfs.graph_destroy(g)
+
+
+@pytest.mark.parametrize("d", [1, 31, 32])
+@pytest.mark.parametrize("k", [1, 8, 64])
+def test_batch_narrow_levels_in_one_launch(d, k):
+    """Consecutive narrow push levels of a multi-source traversal run in one launch on graphs of low
+    degree. A ternary tree under d paths (frontiers that triple, past a member's list of 448 and the
+    4096 vertices of such a level, then thin out) with a tail past the 16 kept levels and a comb of
+    joined paths; rows, level sizes and counts against the oracle, under both rules, push-only and
+    forced schedules that interrupt the narrow levels."""
+    src, dst, V = [], [], 1
+    level = [0]
+    for _ in range(9):  # 1, 3, 9 .. 19683 vertices
+        nxt = []
+        for u in level:
+            for _ in range(3):
+                src.append(u)
+                dst.append(V)
+                nxt.append(V)
+                V += 1
+        level = nxt
+    ends = level[:40 * d]
+    for j in range(22):  # tails of 22 vertices under some leaves, neighbours joined at every fifth
+        new = list(range(V, V + len(ends)))
+        V += len(ends)
+        src += ends
+        dst += new
+        if j % 5 == 4:
+            src += new[:-1]
+            dst += new[1:]
+        ends = new
+    hg = gen.from_edges(V, src, dst, directed=False, name="tree%d" % d)
+    g = upload(hg)
+    rng = np.random.default_rng(k)
+    srcs = [0] + [int(x) for x in rng.integers(0, V, k - 1)]
+    if k >= 8:
+        srcs[-1] = srcs[1]  # a repeated source
+    for opt, tag in ((dobfs.make_options("push_only"), "push_only"), (dobfs.make_options("full"), "ratio"),
+                     (dobfs.make_options("full", dobfs.HEUR_EDGES, 1 / 14, 1 / 24), "edges"),
+                     (dobfs.make_options("full", forced_dirs=[PUSH] * 5 + [PULL] + [PUSH] * 12 + [PULL, PULL]), "forced"),
+                     (dobfs.make_options("pull_only", forced_dirs=[PUSH] * 20), "forced pull_only")):
+        _say(hg.name, "k=%d" % k, tag)
+        d_, st = _run(g, srcs, opt)
+        _check(hg, srcs, d_, st, tag)
+        lv = dobfs.stats_levels(st)
+        R = np.stack([_ref(hg, s) for s in srcs])
+        outdeg = hg.out_degree()
+        for L, row in enumerate(lv):
+            if row["dir"] == PUSH:
+                want = int(outdeg[(R == L).any(axis=0)].sum())
+                assert row["edges"] == row["m_f"] == want, "%s level %d" % (tag, L)
+        d2, _ = _run(g, srcs, opt)
+        assert np.array_equal(d2, d_), tag
+    dobfs.graph_destroy(g)
