@@ -345,7 +345,7 @@ dobfs_status dobfs_bfs_batch(dobfs_graph g, const int32_t *sources, int32_t k,
  * each on a host thread and HIP stream of its own, so queries that arrive
  * while a batch is on the GPU are admitted into the next free slot and run
  * beside it (continuous batching, not a single queue). Graphs whose batches
- * have taken more than 2 ms on average may occupy at most slots - 1 slots at
+ * have taken more than 2 ms, or 256 levels, on average may occupy at most slots - 1 slots at
  * once, so a deep traversal never holds every slot, and their queries are
  * batched only once 8 of them are queued (fewer run one per slot). Admission by memory: the
  * server makes one device allocation of mem_budget bytes when it is created

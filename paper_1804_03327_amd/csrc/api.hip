@@ -51,6 +51,7 @@ struct dobfs_graph_s {
 namespace {
 
 thread_local std::string t_last_error;
+thread_local int64_t t_last_levels = 0;  // levels of the thread's last finished traversal
 
 dobfs_status fail(dobfs_status s, const char* fmt, ...) {
   char buf[512];
@@ -764,6 +765,7 @@ dobfs_status run_steps(std::atomic<int32_t>& last_steps, hipStream_t s, bool tim
   int32_t k_end = 0;
   while (k_end + 1 < batch && !rep->steps[k_end].done) ++k_end;
   last_steps.store(int32_t(s0) + k_end + 1, std::memory_order_relaxed);
+  t_last_levels = res->levels;
   // a launch that ran several levels counts as the steps they take alone
   if (!pd) res->n_main = int32_t(std::max<int64_t>(res->n_main, steps_alone));
   return DOBFS_OK;
@@ -1327,6 +1329,8 @@ dobfs_status dobfs::bfs_batch_rows(dobfs_graph g, const int32_t* sources, int32_
   }
   return DOBFS_OK;
 }
+
+int64_t dobfs::last_levels() { return t_last_levels; }
 
 dobfs_status dobfs::set_error(dobfs_status s, const char* what) { return fail(s, "%s", what); }
 

@@ -547,6 +547,8 @@ hipError_t launch_sort_filter(hipStream_t s, const uint32_t* keys, const int32_t
 dobfs_status bfs_batch_rows(dobfs_graph g, const int32_t* sources, int32_t k, const dobfs_options* opt,
                             const DepthRows& rows, void* workspace, size_t ws_bytes, void* stream,
                             dobfs_stats* stats);
+// Levels the calling thread's last finished traversal ran (not the sort-based pushes).
+int64_t last_levels();
 // Options a multi-source traversal accepts (sets the thread's last error otherwise).
 dobfs_status check_batch_options(const dobfs_options& opt);
 // Records `what` as the calling thread's last error and returns s.

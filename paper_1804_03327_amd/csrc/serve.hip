@@ -12,7 +12,7 @@
 // Queries that arrive while a batch is on the GPU go to the next free slot,
 // so their traversal overlaps the running one on the device. Graphs whose
 // batches have been taking long (a running mean of their service times above
-// kLongMs) may hold at most slots - 1 slots at once, so one slot stays free for
+// kLongMs, or of their level counts above kLongLevels) may hold at most slots - 1 slots at once, so one slot stays free for
 // the others' queries instead of queueing them behind deep traversals; and
 // their queries are batched only once kLongBatchMin of them are queued, fewer
 // going one per slot: on a deep graph a multi-source traversal of a few
@@ -38,9 +38,12 @@ namespace {
 
 constexpr int kMaxSlots = 16;
 constexpr double kLongMs = 2.0;  // a graph whose batches take longer than this on average is "long"
-// Fewest queued queries of a long graph that one multi-source traversal takes (2048x2048 grid:
-// 2 / 4 / 8 sources take 84 / 100 / 99 ms together, two single-source traversals on two
-// streams 41 ms, one alone 32 ms).
+// and so is one whose traversals are deeper than this on average: 0.6 to 1 ms of narrow levels or
+// more, most of the chip idle, against about 0.1 ms for the shallow graphs a slot is kept free for
+constexpr double kLongLevels = 256.0;
+// Fewest queued queries of a long graph that one multi-source traversal takes (measured before
+// narrow levels shared launches; 2048x2048 grid: 2 / 4 / 8 sources took 84 / 100 / 99 ms together,
+// two single-source traversals on two streams 41 ms, one alone 32 ms, now 12 and 12 ms).
 constexpr int32_t kLongBatchMin = 8;
 
 // First-fit allocator over one device allocation, in 256-byte units.
@@ -104,6 +107,7 @@ struct GraphInfo {
   int32_t V = 0;
   int64_t nnz = 0;
   double mean_ms = 0.0;  // running mean of this graph's batch service times (0: none yet)
+  double mean_levels = 0.0;  // and of their level counts
   int32_t running = 0;   // slots running a batch of this graph
 };
 
@@ -149,7 +153,7 @@ size_t run_bytes(dobfs_graph g, const dobfs_options& opt, int32_t k) {
   return batch_bytes(g, k);
 }
 
-bool is_long(const GraphInfo& g) { return g.mean_ms > kLongMs; }
+bool is_long(const GraphInfo& g) { return g.mean_ms > kLongMs || g.mean_levels > kLongLevels; }
 
 // The graph a free slot serves next: that of the oldest queued query, skipping
 // long graphs while slots - 1 slots already run long batches; -1 if none may go.
@@ -228,13 +232,16 @@ void worker(dobfs_server s, int slot) {
                            s->streams[size_t(slot)], nullptr)
                : bfs_batch_rows(s->graphs[gi], src.data(), k, &s->opt.opt, rows, ws, need,
                                 s->streams[size_t(slot)], nullptr);
+    const double levels = st == DOBFS_OK ? double(last_levels()) : 0.0;
     // a later batch may reuse this memory from another stream: the traversal's last kernels
     // may still read their control block after the results are final
     (void)hipStreamSynchronize(s->streams[size_t(slot)]);
     lk.lock();
     s->pool.give(off, need);
     const double t_done = s->now_ms();
-    info.mean_ms = info.mean_ms == 0.0 ? (t_done - t_start) : 0.75 * info.mean_ms + 0.25 * (t_done - t_start);
+    const bool first = info.mean_ms == 0.0;
+    info.mean_ms = first ? (t_done - t_start) : 0.75 * info.mean_ms + 0.25 * (t_done - t_start);
+    info.mean_levels = first ? levels : 0.75 * info.mean_levels + 0.25 * levels;
     --info.running;
     if (lng) --s->long_running;
     for (uint64_t id : take) {
