@@ -206,9 +206,9 @@ __device__ __forceinline__ void cull_reset(LocalShared& sh) {
 }
 
 // True when target w is new to this block's table (and enters it).
-__device__ __forceinline__ bool cull_enter(LocalShared& sh, int32_t w) {
+__device__ __forceinline__ bool cull_enter(uint32_t* table, int32_t w) {
   const uint32_t h = (uint32_t(w) * 2654435761u) >> (32 - kCullBits);
-  return atomicExch(&sh.cull[h], uint32_t(w)) != uint32_t(w);
+  return atomicExch(&table[h], uint32_t(w)) != uint32_t(w);
 }
 
 struct LocalAcc {
@@ -273,7 +273,7 @@ __device__ __forceinline__ void local_unit_chunks(const ExpandArgs& a, LocalShar
     if (cull) {
 #pragma unroll
       for (int t = 0; t < kExpandEPT; ++t)
-        if (valid[t]) valid[t] = cull_enter(sh, w[t]);
+        if (valid[t]) valid[t] = cull_enter(sh.cull, w[t]);
     }
     uint32_t seen[kExpandEPT];
 #pragma unroll
@@ -355,6 +355,120 @@ __device__ __forceinline__ void local_expand_body(const ExpandArgs& a, LocalShar
                       uint32_t(per_unit) * kExpandChunk, cull, acc);
   }
   local_finish(a, sh, acc, 0);
+}
+
+// The push over a frontier list on graphs whose rows have at most kMapDeg entries (meshes): two
+// threads a vertex, so no degree prefix and no search, and a block's 128 vertices are one round.
+// The winners' row extents are loaded beside the claims (in the general form after them), and the
+// block reserves its room in the next list while it writes their results. On the 256^3 lattice at 65 k
+// frontier vertices the general form spent, of some 28 k cycles per block, 7.4 k on prefix, search and
+// neighbours, 6.1 k on claims, 4.9 k on the winners' extents and stores and 5.7 k waiting for its
+// reservation behind 500 other blocks.
+constexpr int kMapDeg = 2 * kExpandEPT;
+struct MapShared {
+  uint32_t cull[1 << kCullBits];
+  uint32_t wave[kThreads / 64], red[4], base;
+};
+__device__ __forceinline__ void mapped_expand_body(const ExpandArgs& a, MapShared& sh, int32_t bid, int32_t nblk) {
+  constexpr int32_t kUnit = kThreads / 2;
+  const int tid = threadIdx.x;
+  const int32_t nf = a.nf;
+  const int32_t nunits = (nf + kUnit - 1) / kUnit;
+  if (bid >= nunits) return;  // no work: no counters to add
+  const bool cull = nf >= kCullMinFrontier;
+  if (cull)
+    for (int i = tid; i < (1 << kCullBits); i += kThreads) sh.cull[i] = kCullNone;
+  if (tid < 4) sh.red[tid] = 0;
+  uint32_t won_total = 0, mnew = 0, insub = 0, edges = 0, maxdeg = 0;
+  const bool two_degrees = a.in_colptr && a.in_colptr != a.out_rowptr;
+  for (int32_t un = bid; un < nunits; un += nblk) {
+    const int32_t i = un * kUnit + (tid >> 1);
+    int32_t u = 0, b = 0, d = 0;
+    if (i < nf) {
+      u = a.Q[i];
+      b = a.rowptr[u] + (tid & 1);
+      d = a.rowptr[u + 1] - b;
+    }
+    const int32_t n = d > 0 ? (d + 1) >> 1 : 0;  // entries b, b + 2, ..
+    edges += uint32_t(n);
+    int32_t w[kExpandEPT];
+    bool live[kExpandEPT];
+#pragma unroll
+    for (int t = 0; t < kExpandEPT; ++t) {
+      live[t] = t < n;
+      w[t] = live[t] ? a.colind[b + 2 * t] : 0;
+    }
+    __syncthreads();  // the table is empty (first unit), base and wave are free (later ones)
+    if (cull) {
+#pragma unroll
+      for (int t = 0; t < kExpandEPT; ++t)
+        if (live[t]) live[t] = cull_enter(sh.cull, w[t]);
+    }
+    uint32_t seen[kExpandEPT], old[kExpandEPT];
+    int32_t rb[kExpandEPT], re[kExpandEPT];
+#pragma unroll
+    for (int t = 0; t < kExpandEPT; ++t) seen[t] = live[t] ? a.claim[w[t] >> 5] : 0xffffffffu;
+#pragma unroll
+    for (int t = 0; t < kExpandEPT; ++t) {
+      const uint32_t bit = 1u << (w[t] & 31);
+      old[t] = 0xffffffffu;
+      rb[t] = re[t] = 0;
+      if (!(seen[t] & bit)) {
+        old[t] = atomicOr(a.claim + (w[t] >> 5), bit);
+        if (a.out_rowptr) {
+          rb[t] = a.out_rowptr[w[t]];
+          re[t] = a.out_rowptr[w[t] + 1];
+        }
+      }
+    }
+    uint32_t c = 0;
+#pragma unroll
+    for (int t = 0; t < kExpandEPT; ++t) c += (old[t] & (1u << (w[t] & 31))) ? 0u : 1u;
+    const uint32_t incl = wave_scan_dpp(c, OpAdd{});
+    if (lane() == 63) sh.wave[tid >> 6] = incl;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int k = 0; k < kThreads / 64; ++k) {
+      const uint32_t t = sh.wave[k];
+      before += k < (tid >> 6) ? t : 0u;
+      all += t;
+    }
+    if (tid == 0 && all) sh.base = atomicAdd(a.qcount, all);
+    won_total += c;
+#pragma unroll
+    for (int t = 0; t < kExpandEPT; ++t) {
+      if (old[t] & (1u << (w[t] & 31))) continue;
+      a.depth[w[t]] = a.level + 1;
+      if (a.parent) a.parent[w[t]] = u;
+      const uint32_t dw = uint32_t(re[t] - rb[t]);
+      mnew += dw;
+      maxdeg = max(maxdeg, dw);
+      if (two_degrees) insub += uint32_t(a.in_colptr[w[t] + 1] - a.in_colptr[w[t]]);
+    }
+    __syncthreads();
+    uint32_t p = sh.base + before + incl - c;
+#pragma unroll
+    for (int t = 0; t < kExpandEPT; ++t)
+      if (!(old[t] & (1u << (w[t] & 31)))) a.Qout[p++] = w[t];
+  }
+  // the block's counters: every total is below 2^31
+  const uint32_t v[4] = {wave_sum(won_total), wave_sum(edges), wave_sum(mnew), two_degrees ? wave_sum(insub) : 0u};
+  const uint32_t md = wave_max32(maxdeg);
+  __shared__ uint32_t s_max;
+  if (tid == 0) s_max = 0;
+  __syncthreads();
+  if (lane() == 0) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (v[k]) atomicAdd(&sh.red[k], v[k]);
+    atomicMax(&s_max, md);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    stripe_add(a.slot, sh.red[0], 0, sh.red[1], sh.red[2], a.in_colptr ? (two_degrees ? sh.red[3] : sh.red[2]) : 0u);
+    stripe_max(a.slot, s_max);
+  }
 }
 
 // Push over the frontier a pull left as bits (a.front), when no pull tile
@@ -801,6 +915,7 @@ __global__ __launch_bounds__(kThreads) void k_level_prep(BfsArgs a, int32_t L, i
 union LevelShared {
   ExpandShared e;
   LocalShared l;
+  MapShared m;
   PullShared p;
 };
 
@@ -983,7 +1098,10 @@ __device__ __forceinline__ void step_body(const BfsArgs& a, const LevelState& st
       bitmap_expand_body(e, a.nwords, a.V, sh.l, bid, nblk);
     } else {
       const ExpandArgs e = step_expand_args(a, st, s, 0u, nullptr, nullptr, nullptr);
-      local_expand_body(e, sh.l, bid, nblk);
+      if (a.max_outdeg <= uint32_t(kMapDeg))
+        mapped_expand_body(e, sh.m, bid, nblk);
+      else
+        local_expand_body(e, sh.l, bid, nblk);
     }
   } else {
     const int32_t tiles = (a.nwords + a.pull_words - 1) / a.pull_words;
