@@ -643,6 +643,7 @@ __device__ __forceinline__ void publish_step(Ctrl* c, int32_t s, const LevelStat
     c->burst.joined[(s + 2) % kSlots][0] = 0;
     c->burst.members[(s + 2) % kSlots][0] = 0;
   }
+  if (threadIdx.x < kListSegs) c->seg[(s + 2) % kSlots][threadIdx.x].n = 0;
   for (int k = threadIdx.x; k < kStripes; k += blockDim.x) zero_stripe(c->slot[(s + 2) % kSlots].s[k]);
 }
 
@@ -692,6 +693,32 @@ __device__ __forceinline__ bool grid_barrier(GridBar* bar, uint32_t target, uint
   __syncthreads();
   return s_ok != 0;
 }
+
+// Where entry i of a list in segments is: the segments' lengths go one to each of 16 lanes and
+// from there to scalars, once a block; a lookup is then 15 compares.
+struct ListMap {
+  uint32_t end[kListSegs];  // entries up to the end of each segment
+  uint32_t cap;
+  __device__ __forceinline__ void load(const ListSeg* seg, uint32_t seg_cap, uint32_t nf) {
+    cap = seg_cap;
+    uint32_t n = 0;
+    if (seg && lane() < kListSegs) n = seg[lane()].n;
+    const uint32_t e = wave_scan_dpp(n, OpAdd{});
+#pragma unroll
+    for (int k = 0; k < kListSegs; ++k) end[k] = seg ? uint32_t(__builtin_amdgcn_readlane(int(e), k)) : nf;
+  }
+  __device__ __forceinline__ uint32_t at(uint32_t i) const {
+    uint32_t first = 0, base = 0;
+#pragma unroll
+    for (int k = 0; k + 1 < kListSegs; ++k) {
+      if (i >= end[k]) {
+        first = end[k];
+        base = uint32_t(k + 1) * cap;
+      }
+    }
+    return base + (i - first);
+  }
+};
 
 // ------------------------------------------------- bursts: what both kinds share
 constexpr uint32_t kBurstEdges = 1024;       // most out-edges of a burst level, per member

@@ -112,6 +112,16 @@ struct BurstCtl {
 };
 constexpr uint32_t kBurstClosed = 1u << 31;
 
+// The list a push of the step loops leaves, in up to kListSegs segments, each with an append
+// counter on a line of its own: segment j starts at j * list_seg_cap(V). Several are used only by
+// the push that maps rows to threads (mapped_expand_body), where no segment can outgrow its share;
+// elsewhere the list is segment 0, whatever its length.
+constexpr int kListSegs = 16;
+struct alignas(128) ListSeg {
+  uint32_t n;
+};
+__host__ __device__ inline uint32_t list_seg_cap(int32_t V) { return uint32_t(V) / uint32_t(kListSegs); }
+
 struct Ctrl {
   unsigned long long ticket[2];  // scan tile tickets, one counter per level (or step) parity
   uint32_t mf32;                 // m_f of the latest frontier scan (expand reads it)
@@ -128,6 +138,7 @@ struct Ctrl {
   LevelSlot tail;                // after a traversal: out-degree sum of the reached vertices (edges)
   GridBar bar;                   // the persistent loops' grid barrier
   BurstCtl burst;
+  ListSeg seg[kSlots][kListSegs];  // step loops: the list step s appends to (slot s % kSlots)
 };
 static_assert(sizeof(Stripe) == 128, "stripe layout");
 static_assert(offsetof(Ctrl, slot) % 128 == 0, "slots start on a line");
@@ -292,6 +303,9 @@ struct ExpandArgs {
   int32_t level;
   int32_t* Qout;             // nullable: winners appended here
   uint32_t* qcount;          // append counter for Qout
+  const ListSeg* seg_in;     // mapped push: the segments of Q (nullptr: one, of nf entries)
+  ListSeg* seg_out;          // mapped push: the segments of Qout
+  uint32_t seg_cap;          // list_seg_cap(V)
   uint32_t* found_out;       // nullable: winners' bits also set here
   const int32_t* rowptr;     // CSR(A) offsets (local push: degrees of the frontier)
   const int32_t* out_rowptr; // nullable: out-degrees of winners -> mnew

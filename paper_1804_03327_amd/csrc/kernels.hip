@@ -360,7 +360,7 @@ __device__ __forceinline__ void local_expand_body(const ExpandArgs& a, LocalShar
 // The push over a frontier list on graphs whose rows have at most kMapDeg entries (meshes): two
 // threads a vertex, so no degree prefix and no search, and a block's 128 vertices are one round.
 // The winners' row extents are loaded beside the claims (in the general form after them), and the
-// block reserves its room in the next list while it writes their results. On the 256^3 lattice at 65 k
+// block reserves its room in the next list, in one of several segments, while it writes their results. On the 256^3 lattice at 65 k
 // frontier vertices the general form spent, of some 28 k cycles per block, 7.4 k on prefix, search and
 // neighbours, 6.1 k on claims, 4.9 k on the winners' extents and stores and 5.7 k waiting for its
 // reservation behind 500 other blocks.
@@ -381,11 +381,15 @@ __device__ __forceinline__ void mapped_expand_body(const ExpandArgs& a, MapShare
   if (tid < 4) sh.red[tid] = 0;
   uint32_t won_total = 0, mnew = 0, insub = 0, edges = 0, maxdeg = 0;
   const bool two_degrees = a.in_colptr && a.in_colptr != a.out_rowptr;
+  ListMap map;
+  map.load(a.seg_in, a.seg_cap, uint32_t(nf));
+  // several segments when none of them can outgrow its share: a level finds at most m vertices
+  const int seg = a.m <= a.seg_cap ? bid % kListSegs : 0;
   for (int32_t un = bid; un < nunits; un += nblk) {
     const int32_t i = un * kUnit + (tid >> 1);
     int32_t u = 0, b = 0, d = 0;
     if (i < nf) {
-      u = a.Q[i];
+      u = a.Q[map.at(uint32_t(i))];
       b = a.rowptr[u] + (tid & 1);
       d = a.rowptr[u + 1] - b;
     }
@@ -434,7 +438,7 @@ __device__ __forceinline__ void mapped_expand_body(const ExpandArgs& a, MapShare
       before += k < (tid >> 6) ? t : 0u;
       all += t;
     }
-    if (tid == 0 && all) sh.base = atomicAdd(a.qcount, all);
+    if (tid == 0 && all) sh.base = uint32_t(seg) * a.seg_cap + atomicAdd(&a.seg_out[seg].n, all);
     won_total += c;
 #pragma unroll
     for (int t = 0; t < kExpandEPT; ++t) {
@@ -819,6 +823,7 @@ __global__ __launch_bounds__(kThreads) void k_bfs_init(BfsArgs a, int32_t source
     if (threadIdx.x < kBarGroups) c->bar.group[threadIdx.x].n = 0;
     for (int k = threadIdx.x; k < 2 * kBurstBlocks * kBurstWords; k += blockDim.x)
       (&c->burst.rec[0][0][0])[k] = 0;
+    if (threadIdx.x < kSlots * kListSegs) c->seg[threadIdx.x / kListSegs][threadIdx.x % kListSegs].n = 0;
     if (threadIdx.x < kSlots) {
       c->burst.joined[threadIdx.x][0] = 0;
       c->burst.members[threadIdx.x][0] = 0;
@@ -1056,7 +1061,10 @@ __device__ __forceinline__ ExpandArgs step_expand_args(const BfsArgs& a, const L
   e.parent = a.parent;
   e.level = L;
   e.Qout = a.Q[(L + 1) % 2];
-  e.qcount = &c->qcount[s % kSlots];
+  e.qcount = &c->seg[s % kSlots][0].n;
+  e.seg_in = s > 0 ? c->seg[(s - 1) % kSlots] : nullptr;
+  e.seg_out = c->seg[s % kSlots];
+  e.seg_cap = list_seg_cap(a.V);
   e.found_out = a.need_F ? a.F[(L + 1) % 2] : nullptr;
   e.rowptr = a.rowptr;
   // winners' out-degrees: the next level's m_f (edge-count rule) and its largest degree
@@ -1097,7 +1105,7 @@ __device__ __forceinline__ void step_body(const BfsArgs& a, const LevelState& st
                                             a.edge_rule ? slot : nullptr);  // m_u afresh: pulls skip it
       bitmap_expand_body(e, a.nwords, a.V, sh.l, bid, nblk);
     } else {
-      const ExpandArgs e = step_expand_args(a, st, s, 0u, nullptr, nullptr, nullptr);
+      const ExpandArgs e = step_expand_args(a, st, s, uint32_t(st.active >> 32), nullptr, nullptr, nullptr);
       if (a.max_outdeg <= uint32_t(kMapDeg))
         mapped_expand_body(e, sh.m, bid, nblk);
       else
@@ -1411,6 +1419,7 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
   bool listed = true;        // the frontier is in memory (else in the members' lists)
   bool fetched = false;      // x holds this level's edges
   uint32_t m_f = 0;          // out-edges of the frontier (of one kept in the lists)
+  const int32_t first = st.level;
   BurstEdges x;
   bool failed = false;
   while (true) {
@@ -1421,10 +1430,12 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
       const uint32_t nf = uint32_t(st.nf), per = (nf + n - 1) / n;
       const uint32_t lo = min(r * per, nf), hi = min(lo + per, nf);
       const int32_t* Q = a.Q[p];
+      ListMap map;  // the step before left segments, a burst one
+      map.load(L == first && s > 0 ? c->seg[(s - 1) % kSlots] : nullptr, list_seg_cap(a.V), nf);
       for (uint32_t i0 = lo; i0 < hi; i0 += kBurstCap) {
         nc = int32_t(min(hi - i0, uint32_t(kBurstCap)));
         for (int32_t i = tid; i < nc; i += kThreads) {
-          const int32_t u = agent_load(&Q[i0 + uint32_t(i)]);
+          const int32_t u = agent_load(&Q[map.at(i0 + uint32_t(i))]);
           const int32_t b = a.rowptr[u], d = a.rowptr[u + 1] - b;
           sh.list[p].v[i] = u;
           sh.list[p].beg[i] = b;
@@ -1503,6 +1514,7 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
         z.insub = t.v[kTotInsub];
         z.edges = t.v[kTotEdges];
         z.maxdeg = t.v[kTotMaxdeg];
+        c->seg[s % kSlots][0].n = t.v[kTotWon];
       }
     }
     // shared out anew when a list overflowed, or when one member's part takes more than one round
