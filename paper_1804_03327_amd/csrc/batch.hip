@@ -396,10 +396,15 @@ __device__ __forceinline__ void mb_pull_body(const BatchArgs& a, const LevelStat
       int32_t j[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) j[q] = p + q < lim ? a.rowind[p + q] : -1;
+      // all four words before any is tested: a test between two loads would make them wait for
+      // each other (the row's last round reads up to three words too many)
+      uint64_t f[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) f[q] = xin[max(j[q], 0)];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         if (j[q] < 0 || (acc & need) == need) continue;
-        acc |= xin[j[q]];
+        acc |= f[q];
         ++checks;
       }
       p += 4;
@@ -455,10 +460,10 @@ __device__ __forceinline__ void mb_pull_body(const BatchArgs& a, const LevelStat
 
 // Whether the pull of a level reads the frontier through a filter (mb_pull_sparse): right after
 // a push that listed its winners, while the list is short. Lists past kMbSparseNf entries let
-// more than one entry in eight through a filter of kMbFilterBits bits, and reading the list in
+// more than one entry in sixteen through a filter of kMbFilterBits bits, and reading the list in
 // every block costs more than it saves.
 constexpr int kMbSparseNf = 8192;
-constexpr int kMbFilterBits = 16;
+constexpr int kMbFilterBits = 17;
 constexpr int kMbSparseU = 4;                   // entries a lane reads at once
 constexpr int kMbSparseWin = 64 * kMbSparseU;   // entries of a wave's window
 __device__ __forceinline__ bool mb_sparse_level(const LevelState& st) {
@@ -495,8 +500,9 @@ __device__ __forceinline__ void mb_filter_build(const BatchArgs& a, const LevelS
 // nearly all of those words are zero. So the tile's entries are read as
 // one contiguous run, each wave a window of it at a time with the next window's loads behind it,
 // and looked up in the filter in LDS; the entries it lets through are packed into a list, and the
-// wave takes them 64 at a time (0.12 and 0.15 ms): find the row (a search over the tile's offsets), read the frontier
-// word, OR it into the row's accumulator. Without the packing almost every wave ran the search
+// wave takes them 64 at a time: find the row (a search over the tile's offsets), read the frontier
+// word, OR it into the row's accumulator (0.12 and 0.15 ms). A hub's tile, 70 k entries, then ended
+// 40 us after the others; windows inside one row read together brought 0.09 and 0.10 ms. Without the packing almost every wave ran the search
 // and the word's load for a few of its lanes (0.17 and 0.22 ms).
 // When less than half of the tile's entries belong to rows that still miss a source, a wave takes
 // each of those rows instead, 64 entries at a time.
@@ -546,7 +552,38 @@ __device__ __forceinline__ void mb_pull_sparse(const BatchArgs& a, const LevelSt
     int32_t j[kU];
     uint32_t e0 = uint32_t(wv * kMbSparseWin);
     load(e0, j);
+    // a tile with a hub's row is many windows long and ends last: where a wave's next two windows
+    // lie inside one row it reads them together and needs neither list nor search (what the filter
+    // holds back reads word 0, so that the loads need no branches)
+    const bool heavy = total > 8u * kStep;
+    uint32_t row_end = 0;
+    int32_t row = 0;
     for (; e0 < total; e0 += kStep) {
+      if (heavy) {
+        if (e0 >= row_end) {
+          row = thread_search(sh.off, 0, kMbTileV, uint32_t(base) + e0);
+          row_end = uint32_t(sh.off[row + 1] - base);
+        }
+        if (e0 + kStep + uint32_t(kMbSparseWin) <= row_end) {
+          uint64_t x = 0;
+          do {
+            int32_t jj[2 * kU];
+#pragma unroll
+            for (int q = 0; q < 2 * kU; ++q) jj[q] = ind[e0 + uint32_t(q / kU) * kStep + uint32_t(q % kU * 64 + ln)];
+#pragma unroll
+            for (int q = 0; q < 2 * kU; ++q) jj[q] = filtered(jj[q]) ? jj[q] : -1;
+            uint64_t f[2 * kU];
+#pragma unroll
+            for (int q = 0; q < 2 * kU; ++q) f[q] = Fc[max(jj[q], 0)];
+#pragma unroll
+            for (int q = 0; q < 2 * kU; ++q) x |= jj[q] >= 0 ? f[q] & active : 0ull;
+            e0 += 2u * kStep;
+          } while (e0 + kStep + uint32_t(kMbSparseWin) <= row_end);
+          if (x) atomicOr((unsigned long long*)&sh.acc[row], (unsigned long long)x);
+          if (e0 >= total) break;
+          load(e0, j);
+        }
+      }
       int32_t jn[kU];
       load(e0 + kStep, jn);
       int n = 0;
