@@ -773,13 +773,23 @@ dobfs_status run_steps(std::atomic<int32_t>& last_steps, hipStream_t s, bool tim
 
 // stats->edges_g500 after a single-source traversal into depth: the out-degree sum of the
 // reached vertices, counted on the device, halved for a graph given as undirected.
-// `tail` receives the device's counters (host memory, pinned or not).
+// `tail` receives the device's counters (host memory, pinned or not); with `rep` (pinned) their sum
+// comes back through it instead, and the host spins on it. RMAT-20 with statistics 152 -> 127 us,
+// against a copy and two synchronisations.
 dobfs_status reached_edges(dobfs_graph g, hipStream_t s, Ctrl* ctrl, const int32_t* depth,
-                           dobfs_stats* stats, LevelSlot* tail) {
+                           dobfs_stats* stats, LevelSlot* tail, HostReport* rep) {
   HIPCK(launch_reached_degree(s, g->rowptr, depth, g->V, &ctrl->tail));
-  HIPCK(hipMemcpyAsync(tail, &ctrl->tail, sizeof(LevelSlot), hipMemcpyDeviceToHost, s));
-  HIPCK(hipStreamSynchronize(s));
-  const int64_t sum = int64_t(sum_slot(*tail).edges);
+  int64_t sum = 0;
+  if (rep) {
+    const uint32_t seq = next_report_seq();
+    HIPCK(launch_slot_report(s, &ctrl->tail, rep, seq));
+    HIPCK(wait_report(rep, seq, s));
+    sum = int64_t(rep->edges);
+  } else {
+    HIPCK(hipMemcpyAsync(tail, &ctrl->tail, sizeof(LevelSlot), hipMemcpyDeviceToHost, s));
+    HIPCK(hipStreamSynchronize(s));
+    sum = int64_t(sum_slot(*tail).edges);
+  }
   stats->edges_g500 = g->symmetric ? sum / 2 : sum;
   return DOBFS_OK;
 }
@@ -879,7 +889,7 @@ dobfs_status bfs_sort_push(dobfs_graph g, int32_t source, const dobfs_options& o
     stats->reached = reached;
     stats->launches_main = stats->launches_aux = 0;
     stats->ms_main_all = stats->ms_aux_all = 0.f;
-    return reached_edges(g, s, c, depth, stats, &hc->tail);
+    return reached_edges(g, s, c, depth, stats, &hc->tail, nullptr);
   }
   return DOBFS_OK;
 }
@@ -930,19 +940,20 @@ dobfs_status bfs_steps(dobfs_graph g, int32_t source, const dobfs_options& opt, 
                               INT64_MAX, DOBFS_ERR_INTERNAL, sink, pd, stats, &res);
   if (st != DOBFS_OK) return st;
   if (stats) {
-    if (ev) {
-      HIPCK(hipEventRecord(ev[kEvEnd], s));
-      HIPCK(hipEventSynchronize(ev[kEvEnd]));
-    }
+    if (ev) HIPCK(hipEventRecord(ev[kEvEnd], s));
     stats->levels = int32_t(res.levels);
-    stats->ms_total = ev ? elapsed(ev[kEvStart], ev[kEvEnd]) : 0.f;
-    stats->ms_init = timing ? elapsed(ev[kEvInit0], ev[kEvInit1]) : 0.f;
     stats->reached = 1 + res.sum_new;
     stats->launches_main = res.n_main;
     stats->launches_aux = res.n_aux;
     stats->ms_main_all = res.ms_main_all;
     stats->ms_aux_all = res.ms_aux_all;
-    return reached_edges(g, s, a.ctrl, depth, stats, tail);
+    st = reached_edges(g, s, a.ctrl, depth, stats, tail, sink.dev == sink.host ? sink.host : nullptr);
+    if (st != DOBFS_OK) return st;
+    // the count's report came after the end event on the stream: the interval stands
+    if (ev) HIPCK(hipEventSynchronize(ev[kEvEnd]));
+    stats->ms_total = ev ? elapsed(ev[kEvStart], ev[kEvEnd]) : 0.f;
+    stats->ms_init = timing ? elapsed(ev[kEvInit0], ev[kEvInit1]) : 0.f;
+    return DOBFS_OK;
   }
   return DOBFS_OK;
 }
@@ -1489,7 +1500,7 @@ dobfs_status dobfs_mxv(dobfs_graph g, const uint32_t* x_bits, const int32_t* x_i
     HostReport* host = host_report();
     if (!host) return fail(DOBFS_ERR_OUT_OF_MEMORY, "pinned host buffer");
     const uint32_t seq = next_report_seq();
-    HIPCK(launch_mxv_report(s, out_slot, host, seq));
+    HIPCK(launch_slot_report(s, out_slot, host, seq));
     HIPCK(wait_report(host, seq, s));
     if (y_nnz) *y_nnz = host->nrec;
   } else {

@@ -468,8 +468,9 @@ hipError_t launch_expand(hipStream_t s, const ExpandArgs& a, const uint32_t* m_d
 hipError_t launch_pull(hipStream_t s, const PullArgs& a);
 struct HostReport;
 hipError_t launch_s2d(hipStream_t s, const int32_t* idx, int32_t n, int32_t V, uint32_t* bits);
-// the sum of slot's aux into host->nrec, then host->seq (system-scope release): pinned host memory
-hipError_t launch_mxv_report(hipStream_t s, const LevelSlot* slot, HostReport* host, uint32_t seq);
+// the sums of slot's aux and edges into host->nrec and host->edges, then host->seq (system-scope
+// release): pinned host memory
+hipError_t launch_slot_report(hipStream_t s, const LevelSlot* slot, HostReport* host, uint32_t seq);
 hipError_t launch_mxv_finalize(hipStream_t s, uint32_t* y, const uint32_t* r, int32_t nwords,
                                int32_t V, int accum, LevelSlot* slot);
 // bit v set when row v of the offsets has more than min_len entries
@@ -477,7 +478,8 @@ hipError_t launch_nz_bits(hipStream_t s, const int32_t* ptr, int32_t V, uint32_t
 hipError_t launch_slab(hipStream_t s, const int32_t* ptr, const int32_t* ind, int32_t V, int4* slab,
                        int32_t* head);
 hipError_t launch_max_degree(hipStream_t s, const int32_t* ptr, int32_t V, uint32_t* out);
-// slot->s[*].edges += out-degrees (CSR offsets ptr) of the vertices with depth >= 0; slot zeroed first
+// slot->s[*].edges += out-degrees (CSR offsets ptr) of the vertices with depth >= 0 (the init kernel
+// zeroes Ctrl::tail)
 hipError_t launch_reached_degree(hipStream_t s, const int32_t* ptr, const int32_t* depth, int32_t V,
                                  LevelSlot* slot);
 // What the host needs after a batch of levels: the state after the batch and
@@ -490,6 +492,7 @@ struct HostReport {
   LevelState steps[kMaxBatch];  // the state each step of the batch published
   int32_t nrec;                 // records in rec (levels rec_first ..)
   int32_t error;                // persistent loop: 1 when a grid barrier wait gave up
+  unsigned long long edges;     // launch_slot_report
   unsigned long long t_end;     // persistent loop, timed: device clock when its last block ended
   uint32_t seq;
   LevelRecord rec[kMaxRec];

@@ -820,6 +820,7 @@ __global__ __launch_bounds__(kThreads) void k_bfs_init(BfsArgs a, int32_t source
     Ctrl* c = a.ctrl;
     for (int k = threadIdx.x; k < kSlots * kStripes; k += blockDim.x)
       zero_stripe(c->slot[k / kStripes].s[k % kStripes]);
+    for (int k = threadIdx.x; k < kStripes; k += blockDim.x) zero_stripe(c->tail.s[k]);
     if (threadIdx.x < kBarGroups) c->bar.group[threadIdx.x].n = 0;
     for (int k = threadIdx.x; k < 2 * kBurstBlocks * kBurstWords; k += blockDim.x)
       (&c->burst.rec[0][0][0])[k] = 0;
@@ -1695,11 +1696,13 @@ __global__ __launch_bounds__(kThreads) void k_mxv_init(Ctrl* ctrl, uint64_t* fla
   }
 }
 
-__global__ void k_mxv_report(const LevelSlot* slot, HostReport* host, uint32_t seq) {
-  const uint32_t v = threadIdx.x < kStripes ? slot->s[threadIdx.x].aux : 0u;
-  const uint32_t n = wave_sum(v);
+__global__ void k_slot_report(const LevelSlot* slot, HostReport* host, uint32_t seq) {
+  const bool in = threadIdx.x < kStripes;
+  const uint32_t n = wave_sum(in ? slot->s[threadIdx.x].aux : 0u);
+  const unsigned long long e = wave_sum64(in ? slot->s[threadIdx.x].edges : 0ull);
   if (threadIdx.x == 0) {
     host->nrec = int32_t(n);
+    host->edges = e;
     __threadfence_system();
     __hip_atomic_store(&host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
@@ -1787,10 +1790,6 @@ __global__ __launch_bounds__(kThreads) void k_reached_degree(const int32_t* ptr,
   if (threadIdx.x == 0 && v[0]) atomicAdd(&slot->s[blockIdx.x % kStripes].edges, v[0]);
 }
 
-__global__ void k_zero_slot(LevelSlot* slot) {
-  for (int k = threadIdx.x; k < kStripes; k += blockDim.x) zero_stripe(slot->s[k]);
-}
-
 __global__ __launch_bounds__(kThreads) void k_check_offsets(const int32_t* ptr, int32_t V, int64_t nnz,
                                                             int32_t* err) {
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
@@ -1872,8 +1871,8 @@ hipError_t launch_mxv_init(hipStream_t s, Ctrl* ctrl, uint64_t* flagsA, uint64_t
   return hipGetLastError();
 }
 
-hipError_t launch_mxv_report(hipStream_t s, const LevelSlot* slot, HostReport* host, uint32_t seq) {
-  hipLaunchKernelGGL(k_mxv_report, dim3(1), dim3(64), 0, s, slot, host, seq);
+hipError_t launch_slot_report(hipStream_t s, const LevelSlot* slot, HostReport* host, uint32_t seq) {
+  hipLaunchKernelGGL(k_slot_report, dim3(1), dim3(64), 0, s, slot, host, seq);
   return hipGetLastError();
 }
 
@@ -1931,7 +1930,6 @@ hipError_t launch_max_degree(hipStream_t s, const int32_t* ptr, int32_t V, uint3
 
 hipError_t launch_reached_degree(hipStream_t s, const int32_t* ptr, const int32_t* depth, int32_t V,
                                  LevelSlot* slot) {
-  hipLaunchKernelGGL(k_zero_slot, dim3(1), dim3(64), 0, s, slot);
   hipLaunchKernelGGL(k_reached_degree, dim3(grid_for(V, kThreads * 8, 512)), dim3(kThreads), 0, s, ptr,
                      depth, V, slot);
   return hipGetLastError();
