@@ -136,7 +136,8 @@ enum {
 
 enum {
   DOBFS_OPT_TIME_KERNELS = 1u, /* every kernel launch records its own start and end (HIP
-                                  extended-launch events); fills the *_ms stats. In the
+                                  extended-launch events), and no launch runs more than one
+                                  level; fills the *_ms stats. In the
                                   persistent loop a level's time is the difference of the
                                   device clock at the starts of consecutive steps */
   DOBFS_OPT_PERSISTENT = 2u /* dobfs_bfs, dobfs_bfs_static and dobfs_bfs_batch: run the level
@@ -284,7 +285,7 @@ dobfs_status dobfs_bfs(dobfs_graph g, int32_t source, const dobfs_options *opt, 
  * synchronises `stream` once per batch of levels.
  * Results, arguments and errors as dobfs_bfs, and:
  *  - the graph must fit: 16*V + 4*ceil(V/32)*4 + 4*(nnz/1024) bytes plus
- *    about 200 KB of control data (256-byte aligned regions) within the
+ *    about 250 KB of control data (256-byte aligned regions) within the
  *    array; V <= 2^22 with nnz <= 2^28 always fits (RMAT scale 22, edge
  *    factor 16). Larger graphs -> INVALID_ARG, nothing written;
  *  - DOBFS_MODE_PUSH_SORT and DOBFS_OPT_TIME_KERNELS -> UNSUPPORTED (they
