@@ -822,8 +822,8 @@ __global__ __launch_bounds__(kThreads) void k_bfs_init(BfsArgs a, int32_t source
       zero_stripe(c->slot[k / kStripes].s[k % kStripes]);
     for (int k = threadIdx.x; k < kStripes; k += blockDim.x) zero_stripe(c->tail.s[k]);
     if (threadIdx.x < kBarGroups) c->bar.group[threadIdx.x].n = 0;
-    for (int k = threadIdx.x; k < 2 * kBurstBlocks * kBurstWords; k += blockDim.x)
-      (&c->burst.rec[0][0][0])[k] = 0;
+    if (a.low_degree)  // (elsewhere bursts have one member)
+      for (int k = threadIdx.x; k < 2 * kBurstBlocks * kBurstWords; k += blockDim.x) (&c->burst.rec[0][0][0])[k] = 0;
     if (threadIdx.x < kSlots * kListSegs) c->seg[threadIdx.x / kListSegs][threadIdx.x % kListSegs].n = 0;
     if (threadIdx.x < kSlots) {
       c->burst.joined[threadIdx.x][0] = 0;
@@ -1403,8 +1403,8 @@ __device__ __forceinline__ LevelState burst_next(const BfsArgs& a, int32_t force
 
 // Step s from its level st on (candidate blocks): levels while they fit and stay below level_end.
 // Block 0 leaves what a step that ran the last of them alone would leave (its state, its counters,
-// the records of the levels before), or, when the traversal ended, the final state; then the
-// report, when the step has one to write.
+// the records of the levels before), or, when the traversal ended, the final state for the next
+// step to find; then the report, when the step has one to write.
 __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32_t s, const StepReportArgs& rp,
                                           BurstShared& sh) {
   Ctrl* c = a.ctrl;
@@ -1523,10 +1523,7 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
     listed = t.v[kTotSpilled] != 0 ||
              (t.v[kTotPart] > kBurstEven && t.v[kTotPart] * n * 2u > 3u * burst_part(t.v[kTotWon], t.v[kTotMnew]));
     if (!next.done && (listed || !go_on)) burst_flush(a, L, base, sh.list[q], nc, sh);
-    if (!go_on) {
-      if (next.done) st = next;
-      break;
-    }
+    if (!go_on) break;
     if (listed) {
       __builtin_amdgcn_s_waitcnt(0);  // this wave's list entries are complete
       __syncthreads();
@@ -1542,6 +1539,8 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
     base += t.v[kTotWon] * uint32_t(listed);
     st = next;
   }
+  // The report names the last level run, never the end: a call returns on the report that does, and
+  // this launch's results are final only when the launch is over. The step after it finds the end.
   if (r == 0 && rp.host) {
     __syncthreads();
     step_report(c, rp, s, st, st, LevelTotals{0, 0, 0, 0, 0, 0}, false, failed ? 1 : 0);
@@ -1550,7 +1549,7 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
 
 // kBurst: the form that may run a burst. It needs more registers than the others' LDS leaves
 // wavefronts for (4 blocks per CU instead of 6), so the host launches it where it expects narrow
-// levels (SingleSteps::burst_form); either form is right for any level.
+// levels (SingleSteps::step); either form is right for any level.
 template <bool EE, bool kBurst>
 __global__ __launch_bounds__(kThreads) void k_step(BfsArgs a, int32_t s, StepReportArgs rp) {
   __shared__ union {
