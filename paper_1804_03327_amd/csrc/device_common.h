@@ -541,7 +541,8 @@ __device__ LevelState next_state(const Args& a, int32_t L, int32_t forced, const
           const int64_t mf_b = tracked ? int64_t(t.mnew) : INT64_MAX;
           const int64_t md_b = tracked ? int64_t(__builtin_amdgcn_readfirstlane(wave_max32(x.maxdeg))) : int64_t(kLocalDeg);
           const int64_t G = main_blocks(a.nwords);
-          if (!batch) {  // what a burst needs to know of the level (sizes; bounds when untracked)
+          if (!batch && level_max_outdeg(a) <= kBurstDeg) {  // what bursts and the mapped push need to know
+            // of the level: its sizes, bounds where they are not tracked (0: no burst on this graph)
             const uint64_t mf_n = tracked ? t.mnew : uint64_t(n_new) * level_max_outdeg(a);
             const uint64_t md_n = tracked ? uint64_t(md_b) : uint64_t(level_max_outdeg(a));
             st.active = ((mf_n < 0xffffffffull ? mf_n : 0xffffffffull) << 32) | md_n;
