@@ -461,13 +461,17 @@ __device__ __forceinline__ void mb_pull_body(const BatchArgs& a, const LevelStat
 // Whether the pull of a level reads the frontier through a filter (mb_pull_sparse): right after
 // a push that listed its winners, while the list is short. Lists past kMbSparseNf entries let
 // more than one entry in sixteen through a filter of kMbFilterBits bits, and reading the list in
-// every block costs more than it saves.
+// every block costs more than it saves. On small graphs a list of more than a sixty-fourth of the
+// vertices has the hubs, so that rows are completed early after all: 11 613 vertices, 4 sources
+// 118 us per launch without this limit, 112 with it, 114 with rows only; 65 521 vertices, 13
+// sources, 134 with it and 137 with rows only. (An eighth: 4% behind rows on a directed graph of
+// 20 000 vertices.)
 constexpr int kMbSparseNf = 8192;
 constexpr int kMbFilterBits = 17;
 constexpr int kMbSparseU = 4;                   // entries a lane reads at once
 constexpr int kMbSparseWin = 64 * kMbSparseU;   // entries of a wave's window
-__device__ __forceinline__ bool mb_sparse_level(const LevelState& st) {
-  return st.local == 1 && st.list_valid && st.nf <= kMbSparseNf;
+__device__ __forceinline__ bool mb_sparse_level(const BatchArgs& a, const LevelState& st) {
+  return st.local == 1 && st.list_valid && st.nf <= min(kMbSparseNf, a.V / 64);
 }
 
 struct MbSparseShared {
@@ -497,13 +501,13 @@ __device__ __forceinline__ void mb_filter_build(const BatchArgs& a, const LevelS
 // them, so nearly every row is read to its end and an early exit saves nothing. A random 8-byte
 // frontier word per in-neighbour is what that costs row by row (64 sources on RMAT-20, 31.4 M
 // in-neighbours, frontiers of 1275 and 2509 vertices: 0.70 and 0.80 ms for that level), and
-// nearly all of those words are zero. So the tile's entries are read as
-// one contiguous run, each wave a window of it at a time with the next window's loads behind it,
-// and looked up in the filter in LDS; the entries it lets through are packed into a list, and the
-// wave takes them 64 at a time: find the row (a search over the tile's offsets), read the frontier
-// word, OR it into the row's accumulator (0.12 and 0.15 ms). A hub's tile, 70 k entries, then ended
-// 40 us after the others; windows inside one row read together brought 0.09 and 0.10 ms. Without the packing almost every wave ran the search
-// and the word's load for a few of its lanes (0.17 and 0.22 ms).
+// nearly all of those words are zero. So the tile's entries are read as one contiguous run, each
+// wave a window of it at a time with the next window's loads behind it, and looked up in the filter
+// in LDS; the entries it lets through are packed into a list, and the wave takes them 64 at a time:
+// find the row (a search over the tile's offsets), read the frontier word, OR it into the row's
+// accumulator (0.12 and 0.15 ms). A hub's tile, 70 k entries, then ended 40 us after the others;
+// windows inside one row read together brought 0.09 and 0.10 ms. Without the packing almost every
+// wave ran the search and the word's load for a few of its lanes (0.17 and 0.22 ms).
 // When less than half of the tile's entries belong to rows that still miss a source, a wave takes
 // each of those rows instead, 64 entries at a time.
 __device__ __forceinline__ void mb_pull_sparse(const BatchArgs& a, const LevelState& st, int32_t s, int32_t tile,
@@ -671,7 +675,7 @@ __device__ __forceinline__ LevelState mb_step_state(const BatchArgs& a, int32_t 
     return st;
   }
   // (the counters' loads are left where the compiler puts them, after the state's: holding
-  // them from the start costs this kernel registers, 6 waves per SIMD instead of 7)
+  // them from the start costs this kernel registers, and it has none to spare for 6 waves per SIMD)
   const StripeLanes x = load_stripes(c->slot[(s - 1) % kSlots]);
   const LevelState prev = c->ring[(s - 1) % kRing];
   *prev_out = prev;
@@ -1276,7 +1280,7 @@ __device__ __forceinline__ void mb_step_body(const BatchArgs& a, const LevelStat
     mb_expand_body(a, st, s, sh.e);
   } else {
     const int32_t ntiles = (a.nwords + kMbTileWords - 1) / kMbTileWords;
-    if (mb_sparse_level(st)) {
+    if (mb_sparse_level(a, st)) {
       if (int32_t(blockIdx.x) >= ntiles) return;
       mb_filter_build(a, st, sh.f);
       for (int32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {

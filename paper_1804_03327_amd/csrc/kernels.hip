@@ -360,10 +360,12 @@ __device__ __forceinline__ void local_expand_body(const ExpandArgs& a, LocalShar
 // The push over a frontier list on graphs whose rows have at most kMapDeg entries (meshes): two
 // threads a vertex, so no degree prefix and no search, and a block's 128 vertices are one round.
 // The winners' row extents are loaded beside the claims (in the general form after them), and the
-// block reserves its room in the next list, in one of several segments, while it writes their results. On the 256^3 lattice at 65 k
-// frontier vertices the general form spent, of some 28 k cycles per block, 7.4 k on prefix, search and
-// neighbours, 6.1 k on claims, 4.9 k on the winners' extents and stores and 5.7 k waiting for its
-// reservation behind 500 other blocks.
+// block reserves its room in the next list, in one of several segments, while it writes their
+// results. On the 256^3 lattice at 65 k frontier vertices the general form spent, of some 28 k
+// cycles per block, 7.4 k on prefix, search and neighbours, 6.1 k on claims, 4.9 k on the winners'
+// extents and stores and 5.7 k waiting for its reservation behind 500 other blocks. A search there:
+// 9.2 ms in the general form, 7.9 in this one, 7.4 with the list in 16 segments. Bound now by the
+// claims (an atomic costs a CU 4 cycles a lane) and the launch per level.
 constexpr int kMapDeg = 2 * kExpandEPT;
 struct MapShared {
   uint32_t cull[1 << kCullBits];

@@ -357,10 +357,11 @@ def test_batch_last_level_pull_after_push(graphs, name):
         assert [x["dir"] for x in dobfs.stats_levels(st)] == sc, tag
 
 
+@pytest.mark.parametrize("room", [3, 63, 64])
 @pytest.mark.parametrize("leaves", [1, 254, 255, 256, 2047, 8191, 8192, 8193])
-def test_batch_pull_after_short_list(leaves):
+def test_batch_pull_after_short_list(leaves, room):
     """A pull right after a push that listed its winners reads the frontier through a filter while
-    the list has at most 8192 entries: a hub joined to `leaves` vertices, every leaf with a tail
+    the list has at most 8192 entries and a 64th of the vertices (room): a hub joined to `leaves` vertices, every leaf with a tail
     of two more and some leaves joined to each other, so that a tile's entries belong to rows that
     still miss a source (the filtered form), or mostly do not, and rows of many and of no entries
     meet in one tile; V is ragged."""
@@ -369,7 +370,7 @@ def test_batch_pull_after_short_list(leaves):
     leaf = np.arange(first, first + leaves)
     mid = leaf + leaves
     end = mid + leaves
-    V = 1 + 3 * leaves + 5  # the last five vertices are isolated
+    V = 1 + room * leaves + 5  # the last five vertices are isolated, with more room others too
     pick = rng.integers(0, leaves, (2, 4 * leaves))
     src = np.concatenate([np.full(leaves, hub), leaf, mid, leaf[pick[0]]])
     dst = np.concatenate([leaf, mid, end, end[pick[1]]])
