@@ -738,6 +738,7 @@ dobfs_status run_steps(std::atomic<int32_t>& last_steps, hipStream_t s, bool tim
         ls.variant = r.variant;
         ls.edges = r.edges;
         ls.m_f = r.m_f;
+        if (!timing) ls.ms_main = ls.ms_aux = 0.f;  // (the steps above name one level a launch)
       }
     }
     rec_first = rep->end.done ? rep->end.levels : rep->end.level;

@@ -579,3 +579,30 @@ def test_narrow_levels_deep():
                 dobfs.bfs(g, s, depth, None, opt)
                 assert np.array_equal(depth.cpu().numpy(), want), hg.name
         dobfs.graph_destroy(g)
+
+
+def test_level_times_zero_without_timing():
+    """Per-level times are 0 on untimed calls, whatever the caller's array held before, also for the
+    levels that shared a launch (a path, a grid) and on a reused array after a timed call."""
+    path = gen.from_edges(300, np.arange(299), np.arange(1, 300), directed=False, name="path300")
+    for hg in (path, gen.grid2d(40, 30), gen.rmat(10, 16, seed=1)):
+        g = upload(hg)
+        depth = torch.empty(g.V, dtype=torch.int32, device="cuda")
+        rows = torch.empty(2 * g.V, dtype=torch.int32, device="cuda")
+        st = dobfs.make_stats(512)
+        calls = [("bfs", lambda o: dobfs.bfs(g, 0, depth, opt=o, stats=st)),
+                 ("bfs persistent", lambda o: dobfs.bfs(g, 0, depth, opt=o, stats=st)),
+                 ("batch", lambda o: dobfs.bfs_batch(g, [0, g.V - 1], rows, opt=o, stats=st)),
+                 ("static", lambda o: dobfs.bfs_static(g, 0, depth, opt=o, stats=st))]
+        for name, call in calls:
+            for fill in ("garbage", "timed"):
+                for x in range(512):
+                    st.level[x].ms_main = st.level[x].ms_aux = 7.0
+                if fill == "timed" and name != "static":
+                    call(dobfs.make_options("push_only", time_kernels=True, persistent=name.endswith("persistent")))
+                    assert any(x["ms_main"] > 0 for x in dobfs.stats_levels(st)), hg.name
+                call(dobfs.make_options("push_only", persistent=name.endswith("persistent")))
+                lv = dobfs.stats_levels(st)
+                bad = sum(1 for x in lv if x["ms_main"] != 0 or x["ms_aux"] != 0)
+                assert st.levels == len(lv) and bad == 0, "%s %s %s: %d of %d" % (hg.name, name, fill, bad, len(lv))
+        dobfs.graph_destroy(g)
