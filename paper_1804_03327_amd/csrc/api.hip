@@ -964,7 +964,12 @@ dobfs_status bfs_steps(dobfs_graph g, int32_t source, const dobfs_options& opt, 
 // loads the library, held until the process ends. Host code never passes the
 // symbol itself to a kernel: its device address on each device comes from
 // hipGetSymbolAddress, taken once per device with that device current.
-constexpr size_t kStaticScratchBytes = DOBFS_STATIC_SCRATCH_BYTES;
+// Which graphs fit is part of the interface: their arrays and kStaticControl bytes within
+// DOBFS_STATIC_SCRATCH_BYTES. The control block and the report may outgrow that share, so the array
+// has room for them whatever they take.
+constexpr size_t kStaticControl = 155008;
+constexpr size_t kStaticScratchBytes = DOBFS_STATIC_SCRATCH_BYTES - kStaticControl +
+                                       (sizeof(Ctrl) + 255) / 256 * 256 + sizeof(HostReport);
 static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes];
 
 std::mutex g_scratch_mu;
@@ -1193,10 +1198,12 @@ dobfs_status dobfs_bfs_static(dobfs_graph g, int32_t source, const dobfs_options
     return fail(DOBFS_ERR_UNSUPPORTED, "kernel timing needs events, which this call does not create");
   const Layout L = plan(g->V, g->nnz);
   const size_t rep_off = align_up(L.total);
-  if (rep_off + sizeof(HostReport) > kStaticScratchBytes)
+  if (L.ctrl + kStaticControl > DOBFS_STATIC_SCRATCH_BYTES)
     return fail(DOBFS_ERR_INVALID_ARG,
                 "graph needs %zu bytes of scratch (V = %d, nnz = %lld); the static scratch holds %zu",
-                rep_off + sizeof(HostReport), g->V, (long long)g->nnz, kStaticScratchBytes);
+                L.ctrl + kStaticControl, g->V, (long long)g->nnz, DOBFS_STATIC_SCRATCH_BYTES);
+  if (rep_off + sizeof(HostReport) > kStaticScratchBytes)
+    return fail(DOBFS_ERR_INTERNAL, "the static scratch has no room for the report");
   DeviceScope ds(g->device);
   if (ds.err != hipSuccess) return hip_fail(ds.err, "hipSetDevice", __LINE__);
   uint8_t* base = nullptr;

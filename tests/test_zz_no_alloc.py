@@ -127,3 +127,23 @@ def test_refusals():
         dobfs.bfs_static(g, g.V, depth)
     assert e.value.status == dobfs.ERR_INVALID_ARG
     dobfs.graph_destroy(g)
+
+
+@pytest.mark.parametrize("V,fits", [(4_309_886, True), (4_310_400, False)])
+def test_static_limit(V, fits):
+    """The largest graphs the call takes: which ones fit does not move with the control data."""
+    src = np.array([0, V - 2])
+    hg = gen.from_edges(V, src, src + 1, directed=False, name="pairs%d" % V)
+    g = upload(hg)
+    depth = torch.full((V,), -7, dtype=torch.int32, device="cuda")
+    if fits:
+        dobfs.bfs_static(g, V - 1, depth)
+        want = np.full(V, -1, dtype=np.int32)
+        want[V - 1], want[V - 2] = 0, 1
+        assert np.array_equal(depth.cpu().numpy(), want)
+    else:
+        with pytest.raises(dobfs.DobfsError) as e:
+            dobfs.bfs_static(g, V - 1, depth)
+        assert e.value.status == dobfs.ERR_INVALID_ARG
+        assert int(depth.max()) == -7
+    dobfs.graph_destroy(g)
