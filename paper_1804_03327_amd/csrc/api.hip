@@ -579,7 +579,7 @@ struct SingleSteps {
   bool narrow_first() const { return a.low_degree != 0; }
   bool narrow_next(const HostReport& r) const {
     const LevelState& st = r.end;
-    return st.dir == DOBFS_DIR_PUSH && uint32_t(st.nf) <= kBurstNf * kBurstBlocks;
+    return st.dir == DOBFS_DIR_PUSH && uint32_t(st.nf) <= kBurstNf * burst_members(a);
   }
   hipError_t before_report(hipStream_t, int32_t) const { return hipSuccess; }
   hipError_t persistent(hipStream_t s, int32_t s_first, int32_t n, int32_t blocks, uint32_t spin_limit,

@@ -486,7 +486,9 @@ __device__ __forceinline__ void stripes_needed(const StripeLanes& x) {
 // a push can share out its own work.
 // prev_slot: the counter slot of the step that ended level L-1 (multi-source: its m_f tells
 // whether that push listed its winners or marked them).
-template <class Args>
+// kSizes: the caller needs a list push's sizes (LevelState::active) on every graph (the form of
+// k_step that runs bursts); else only graphs whose pushes are mapped to threads have them.
+template <bool kSizes = false, class Args>
 __device__ LevelState next_state(const Args& a, int32_t L, int32_t forced, const LevelState& prev,
                                  const StripeLanes& x, int32_t prev_slot, LevelTotals* tot_out) {
   LevelTotals t{0, 0, 0, 0, 0, 0};
@@ -541,8 +543,9 @@ __device__ LevelState next_state(const Args& a, int32_t L, int32_t forced, const
           const int64_t mf_b = tracked ? int64_t(t.mnew) : INT64_MAX;
           const int64_t md_b = tracked ? int64_t(__builtin_amdgcn_readfirstlane(wave_max32(x.maxdeg))) : int64_t(kLocalDeg);
           const int64_t G = main_blocks(a.nwords);
-          if (!batch && level_max_outdeg(a) <= kBurstDeg) {  // what bursts and the mapped push need to know
-            // of the level: its sizes, bounds where they are not tracked (0: no burst on this graph)
+          // what bursts and the mapped push need to know of the level: its sizes, bounds where they
+          // are not tracked (on RMAT-22 their few instructions cost the plain form 0.4%)
+          if (kSizes || (!batch && level_max_outdeg(a) <= uint32_t(kMapDeg))) {
             const uint64_t mf_n = tracked ? t.mnew : uint64_t(n_new) * level_max_outdeg(a);
             const uint64_t md_n = tracked ? uint64_t(md_b) : uint64_t(level_max_outdeg(a));
             st.active = ((mf_n < 0xffffffffull ? mf_n : 0xffffffffull) << 32) | md_n;

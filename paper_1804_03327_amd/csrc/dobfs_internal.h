@@ -52,7 +52,7 @@ struct alignas(64) LevelState {
   int64_t m_u;         // edge-count rule: in-edges of still-unvisited vertices
   uint64_t active;     // multi-source: sources whose frontier entering the level is non-empty;
                        // single source: of a push with local 1, its out-edges << 32 | largest
-                       // out-degree (upper bounds), else 0
+                       // out-degree (upper bounds) where the step needs them (next_state)
   uint64_t t0;         // single source, persistent loop: device clock when the step started
 };
 static_assert(sizeof(LevelState) == 64, "one state per 64-byte line");
@@ -170,6 +170,7 @@ constexpr int kScanBlocksMax = 256;                  // scan grids stride over t
 constexpr int kExpandEPT = 4;                        // expand: edges per thread per chunk
 constexpr int kExpandChunk = kThreads * kExpandEPT; // 1024 edges per chunk
 constexpr int kExpandWin = kExpandChunk + 1;         // frontier entries cached in LDS per chunk
+constexpr int kMapDeg = 2 * kExpandEPT;               // largest out-degree of the push that maps rows to threads
 constexpr int kExpandBuf = 2048;                     // winners buffered in LDS before a list flush
 constexpr int kExpandBlocks = 1024;                  // expand grid (strides over chunks)
 constexpr int kPullTileWords = 128;                  // pull: most bitmap words owned by a block (measured
@@ -360,6 +361,9 @@ struct BfsArgs {
   int32_t pull_words;        // pull_tile_words(nwords)
   Sched sched;
 };
+// How many members a burst on this graph is for. Where there are hubs a search is narrow for a
+// level or two and then wide at once: the leader runs those alone, and nobody has to join.
+__host__ __device__ inline uint32_t burst_members(const BfsArgs& a) { return a.low_degree ? kBurstBlocks : 1; }
 
 // ---- multi-source BFS: up to 64 sources, one bit of a uint64 per source ----
 constexpr int kMaxSources = 64;

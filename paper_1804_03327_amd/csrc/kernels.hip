@@ -366,7 +366,6 @@ __device__ __forceinline__ void local_expand_body(const ExpandArgs& a, LocalShar
 // extents and stores and 5.7 k waiting for its reservation behind 500 other blocks. A search there:
 // 9.2 ms in the general form, 7.9 in this one, 7.4 with the list in 16 segments. Bound now by the
 // claims (an atomic costs a CU 4 cycles a lane) and the launch per level.
-constexpr int kMapDeg = 2 * kExpandEPT;
 struct MapShared {
   uint32_t cull[1 << kCullBits];
   uint32_t wave[kThreads / 64], red[4], base;
@@ -936,6 +935,8 @@ union LevelShared {
 // step s gather in slot s % kSlots; step s clears slot (s + 2) % kSlots, which
 // nothing reads or writes until step s + 2.
 
+// kSizes: as next_state.
+template <bool kSizes>
 __device__ __forceinline__ LevelState step_state(const BfsArgs& a, int32_t s, LevelTotals* tot, LevelState* prev_out,
                                  bool* new_level) {
   const Ctrl* c = a.ctrl;
@@ -959,7 +960,7 @@ __device__ __forceinline__ LevelState step_state(const BfsArgs& a, int32_t s, Le
   const int32_t L = prev.level + 1;
   const int32_t forced = L < a.n_forced ? int32_t(c->forced[L]) : -1;
   *new_level = true;
-  return next_state(a, L, forced, prev, x, (s - 1) % kSlots, tot);
+  return next_state<kSizes>(a, L, forced, prev, x, (s - 1) % kSlots, tot);
 }
 
 // The last step of a batch writes the batch's report itself (block 0, right
@@ -1199,10 +1200,6 @@ __device__ __forceinline__ bool burst_fits(const LevelState& st, uint32_t mf, ui
   return !st.done && st.dir == 0 && st.local == 1 && st.phase == kPhaseWhole && uint32_t(st.nf) <= kBurstNf * n &&
          mf <= kBurstEdges * n && maxdeg <= kBurstDeg;
 }
-
-// How many members a burst on this graph is for. Where there are hubs a search is narrow for a
-// level or two and then wide at once: the leader runs those alone, and nobody has to join.
-__device__ __forceinline__ uint32_t burst_members(const BfsArgs& a) { return a.low_degree ? kBurstBlocks : 1; }
 
 // Up to kExpandEPT edges a thread works on at once: targets, sources, and the targets' visited
 // words and row extents.
@@ -1561,7 +1558,7 @@ __global__ __launch_bounds__(kThreads) void k_step(BfsArgs a, int32_t s, StepRep
   LevelTotals tot;
   LevelState prev;
   bool new_level;
-  const LevelState st = step_state(a, s, &tot, &prev, &new_level);
+  const LevelState st = step_state<kBurst>(a, s, &tot, &prev, &new_level);
   const bool burst = kBurst && burst_fits(st, uint32_t(st.active >> 32), uint32_t(st.active), burst_members(a));
   if (blockIdx.x == 0) {
     publish_step(a.ctrl, s, st, prev, tot, new_level);
@@ -1600,7 +1597,7 @@ __global__ __launch_bounds__(kThreads) void k_steps(BfsArgs a, int32_t s_first, 
     LevelTotals tot;
     LevelState prev;
     bool new_level;
-    LevelState st = step_state(a, s, &tot, &prev, &new_level);
+    LevelState st = step_state<false>(a, s, &tot, &prev, &new_level);
     if (blockIdx.x == 0) {
       if (timing) st.t0 = wall_clock64();
       publish_step(a.ctrl, s, st, prev, tot, new_level);

@@ -5,6 +5,7 @@ Graph500-style validator, and on pull levels equal the first in-neighbour one le
 stored CSC order (the early-exit parent). Per-level statistics are checked against the
 oracle's level sizes, the Section 6.3 schedule and the exact work counts (Table 1)."""
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -606,3 +607,34 @@ def test_level_times_zero_without_timing():
                 bad = sum(1 for x in lv if x["ms_main"] != 0 or x["ms_aux"] != 0)
                 assert st.levels == len(lv) and bad == 0, "%s %s %s: %d of %d" % (hg.name, name, fill, bad, len(lv))
         dobfs.graph_destroy(g)
+
+
+def test_hub_level_after_narrow_levels():
+    """A chain of 200 vertices into a hub of 500 000 leaves: the levels of the chain are narrow and
+    may share launches, the hub's is one for the whole chip. Timed calls run a level per launch and
+    record two events with each; an untimed one does less on the host and must take less time. With
+    the hub's edges on one block (500 rounds of 1024 edges and an atomic on one counter per leaf,
+    more than 5 ms) it took twice as long."""
+    chain, leaves = 200, 500_000
+    src = np.concatenate([np.arange(chain), np.full(leaves, chain)])
+    dst = np.concatenate([np.arange(1, chain + 1), chain + 1 + np.arange(leaves)])
+    hg = gen.from_edges(chain + 1 + leaves, src, dst, directed=True, name="chainhub")
+    want, _ = oracle.bfs(hg, 0)
+    g = upload(hg)
+    r = BfsRunner(g)
+    for mode in ("push_only", "full"):
+        ms = {}
+        for timed in (False, True):
+            best = []
+            for _ in range(5):
+                torch.cuda.synchronize()
+                t0 = time.perf_counter()
+                r.run(0, mode=mode, time_kernels=timed)
+                torch.cuda.synchronize()
+                best.append(time.perf_counter() - t0)
+                depth, parent = r.result()
+                assert np.array_equal(depth, want) and oracle.validate(hg, 0, depth, parent)[0] == 0, mode
+            ms[timed] = 1e3 * min(best)
+        _say(hg.name, mode, "untimed %.2f ms, timed %.2f ms" % (ms[False], ms[True]))
+        assert ms[False] < ms[True], mode
+    dobfs.graph_destroy(g)
