@@ -23,6 +23,12 @@
 
 using namespace dobfs;
 
+// What a traversal took, a guess for the next of its kind on the graph.
+struct LastRun {
+  std::atomic<int32_t> steps{8};    // launches of the step kernel
+  std::atomic<int32_t> levels{0};
+};
+
 struct dobfs_graph_s {
   int device = 0;
   int32_t V = 0;
@@ -38,8 +44,7 @@ struct dobfs_graph_s {
   int32_t* head = nullptr;          // first entry of every CSC(A) column, complemented when more follow
   uint32_t max_outdeg = 0;          // largest CSR(A) row length
   bool symmetric = false;           // given as undirected: the same arrays for CSR(A) and CSC(A)
-  std::atomic<int32_t> last_steps{8};   // step count of the previous single-source BFS
-  std::atomic<int32_t> last_steps_mb{8};   // the same for multi-source traversals
+  LastRun last, last_mb;            // the previous single-source and multi-source traversal
   void* owned[4] = {nullptr, nullptr, nullptr, nullptr};
   std::mutex mu;                    // guards the internal workspace
   void* ws = nullptr;
@@ -557,13 +562,19 @@ uint32_t env_u32(const char* name, uint32_t dflt) {
 // persistent(): the persistent form of a batch (rp as for step()); grid(): the full grid of a
 // step launch; next_grid(): the blocks for the next batch's launches from the report of the
 // batch before (0: the full grid); capacity(): blocks of the persistent kernel that fit at once.
-constexpr int32_t kBurstLevels = 4096;  // levels the bursts of one batch run at most (about 10 ms of a deep graph)
+//
+// burst_levels: the most levels the bursts of one batch may run. What a batch enqueues is what
+// another stream's kernels wait for when they share its hardware queue (4 a process): 64 launches of
+// a level each take 0.6 to 0.8 ms, and a batch that bursts about the same (4.3 us a level of a 2048 x
+// 2048 grid, 7 to 20 for several sources). Without a bound a whole search of 12 ms was one launch, and
+// queries of small graphs next to it in a server took 7 to 14 ms at the 99th percentile.
 struct SingleSteps {
   const BfsArgs& a;
   bool burst;  // not for timed calls (a level per launch) and the modes whose pushes need the scan
   static constexpr bool self_report = true;
   static constexpr bool needs_records = false;
   static constexpr int32_t push_steps = 1;  // at least
+  static constexpr int32_t burst_levels = kMaxBurstLevels;
   int64_t grid() const { return main_blocks(a.nwords); }
   int64_t next_grid(const HostReport&, int32_t) const { return 0; }
   static int32_t capacity(const PersistentDevice& d) { return d.capacity; }
@@ -594,6 +605,7 @@ struct BatchSteps {
   static constexpr bool self_report = false;
   static constexpr bool needs_records = true;  // next_grid reads them
   static constexpr int32_t push_steps = 2;     // steps of a push level
+  static constexpr int32_t burst_levels = 128;
   int64_t grid() const {
     return std::max<int64_t>(kExpandBlocks, std::min<int64_t>((int64_t(a.nwords) + kMbTileWords - 1) / kMbTileWords, 8192));
   }
@@ -644,7 +656,9 @@ struct BatchSteps {
 // published and the records of the levels that are complete; steps enqueued
 // past the end exit at once. The first batch is one step longer than the
 // previous traversal of the same kind on the graph needed; later batches start
-// at 4 and double. When timing, step k of a batch has events ev_m0(k) /
+// at 4 and double. While launches run several levels each (bursts) of a traversal deeper than
+// one batch's share of them (Steps::burst_levels), a batch is one launch: more would wait behind
+// it with a level each. When timing, step k of a batch has events ev_m0(k) /
 // ev_m1(k); a level's scan step counts as its ms_aux, its other step as its
 // ms_main. With `pd` (persistent loop on that device) a batch is one launch of
 // the persistent kernel running the batch's steps, with the same report;
@@ -652,14 +666,15 @@ struct BatchSteps {
 // launch's end).
 // max_levels: a traversal that reaches that many levels fails with too_deep.
 template <class Steps>
-dobfs_status run_steps(std::atomic<int32_t>& last_steps, hipStream_t s, bool timing, hipEvent_t* ev,
+dobfs_status run_steps(LastRun& last, hipStream_t s, bool timing, hipEvent_t* ev,
                        const Steps& S, const Ctrl* ctrl, int64_t max_steps, int64_t max_levels,
                        dobfs_status too_deep, const ReportSink& sink, PersistentDevice* pd,
                        dobfs_stats* stats, LoopResult* res) {
   HostReport* rep = sink.host;
   int64_t s0 = 0;
   int32_t rec_first = 0;
-  int32_t batch = std::min(std::max(last_steps.load(std::memory_order_relaxed) + 1, 2), kMaxBatch);
+  const int32_t guess = last.steps.load(std::memory_order_relaxed) + 1;
+  int32_t batch = std::min(std::max(guess, 2), kMaxBatch);
   int32_t next_batch = 4;
   auto E = [&](int i) -> hipEvent_t { return timing ? ev[i] : nullptr; };
   const int32_t cap = pd ? Steps::capacity(*pd) : 0;
@@ -672,17 +687,22 @@ dobfs_status run_steps(std::atomic<int32_t>& last_steps, hipStream_t s, bool tim
   int64_t grid = 0;  // blocks of the step launches (0: the full grid)
   int64_t steps_alone = 1;  // steps the levels (and the end) take one per launch
   bool narrow = S.narrow_first();
+  const bool bursts = S.burst && !pd;
+  if (bursts && narrow && last.levels.load(std::memory_order_relaxed) > Steps::burst_levels) {
+    batch = 1;
+    next_batch = std::min(std::max(guess, 4), kMaxBatch);  // where the levels turn wide at once
+  }
   while (true) {
     if (s0 + batch > max_steps) batch = int32_t(max_steps - s0);
     const uint32_t seq = next_report_seq();
     // untimed, the batch's last step writes the report; timed, a report kernel follows the
     // steps so that every step's end event has completed when the host reads it
-    // where the records are not read a burst may run any number of levels; it leaves it to single
-    // steps to reach the level that is too deep
+    // a burst leaves it to single steps to reach the level that is too deep
     const bool records = stats || Steps::needs_records;
     const int32_t rec_from = records ? rec_first : INT32_MAX;
     const int32_t level_end =
-        int32_t(std::min<int64_t>(rec_first + (records ? kMaxRec - batch : kBurstLevels), max_levels - 1));
+        int32_t(std::min<int64_t>(rec_first + Steps::burst_levels, max_levels - 1));
+    const int32_t level_begin = rec_first;
     const StepReportArgs rp{sink.dev, seq, int32_t(s0), rec_from, level_end};
     const StepReportArgs no_report{nullptr, 0u, 0, 0, level_end};
     const bool self = Steps::self_report && !timing;
@@ -759,13 +779,22 @@ dobfs_status run_steps(std::atomic<int32_t>& last_steps, hipStream_t s, bool tim
       return fail(DOBFS_ERR_INTERNAL, "traversal needs more than %lld steps", (long long)max_steps);
     }
     s0 += batch;
-    batch = next_batch;
-    next_batch = std::min(2 * next_batch, kMaxBatch);
+    const int32_t done = batch;
+    if (bursts && narrow && end.level - level_begin > batch) {  // launches run several levels each
+      batch = 1;
+    } else {
+      batch = next_batch;
+      next_batch = std::min(2 * next_batch, kMaxBatch);
+    }
+    // frontiers may outgrow the grid that suits them now if the batch reaches far past this one (64
+    // sources on a 64^3 lattice: 2.86 ms, 3.42 with 64 launches on the grid of one narrow level)
+    if (batch > 2 * done) grid = 0;
   }
   // steps the traversal used, up to the one that found the end (the batch before ended short of it)
   int32_t k_end = 0;
   while (k_end + 1 < batch && !rep->steps[k_end].done) ++k_end;
-  last_steps.store(int32_t(s0) + k_end + 1, std::memory_order_relaxed);
+  last.steps.store(int32_t(s0) + k_end + 1, std::memory_order_relaxed);
+  last.levels.store(int32_t(res->levels), std::memory_order_relaxed);
   t_last_levels = res->levels;
   // a launch that ran several levels counts as the steps they take alone
   if (!pd) res->n_main = int32_t(std::max<int64_t>(res->n_main, steps_alone));
@@ -937,7 +966,7 @@ dobfs_status bfs_steps(dobfs_graph g, int32_t source, const dobfs_options& opt, 
     pd = persistent_device(g->device);
     if (!pd) return fail(DOBFS_ERR_UNSUPPORTED, "the persistent level loop is not available on device %d", g->device);
   }
-  dobfs_status st = run_steps(g->last_steps, s, timing, ev, SingleSteps{a, a.local_push && !timing}, a.ctrl, max_steps,
+  dobfs_status st = run_steps(g->last, s, timing, ev, SingleSteps{a, a.local_push && !timing}, a.ctrl, max_steps,
                               INT64_MAX, DOBFS_ERR_INTERNAL, sink, pd, stats, &res);
   if (st != DOBFS_OK) return st;
   if (stats) {
@@ -1329,7 +1358,7 @@ dobfs_status dobfs::bfs_batch_rows(dobfs_graph g, const int32_t* sources, int32_
     pd = persistent_device(g->device);
     if (!pd) return fail(DOBFS_ERR_UNSUPPORTED, "the persistent level loop is not available on device %d", g->device);
   }
-  st = run_steps(g->last_steps_mb, s, timing, ev, BatchSteps{a, rows, !timing}, a.ctrl, max_steps, cap,
+  st = run_steps(g->last_mb, s, timing, ev, BatchSteps{a, rows, !timing}, a.ctrl, max_steps, cap,
                  cap < int64_t(g->V) + 2 ? DOBFS_ERR_UNSUPPORTED : DOBFS_ERR_INTERNAL, sink, pd, stats, &res);
   if (st != DOBFS_OK) return st;
   if (!stats) return DOBFS_OK;

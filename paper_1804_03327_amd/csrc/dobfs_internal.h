@@ -490,7 +490,9 @@ hipError_t launch_reached_degree(hipStream_t s, const int32_t* ptr, const int32_
 // the records of its levels. Written into pinned host memory by one block,
 // `seq` last (system-scope release), so the host can spin on it.
 constexpr int kMaxBatch = 64;
-constexpr int kMaxRec = kRing - kMaxBatch;  // levels a batch may complete when their records are wanted
+constexpr int kMaxBurstLevels = 192;  // levels the bursts of a batch may run (run_steps)
+constexpr int kMaxRec = kMaxBatch + kMaxBurstLevels;  // levels a batch may complete
+static_assert(kMaxRec <= kRing, "records on the device");
 struct HostReport {
   LevelState end;
   LevelState steps[kMaxBatch];  // the state each step of the batch published

@@ -322,3 +322,43 @@ def test_two_streams_overlap_on_device():
     for r, s in zip(runners, srcs):
         assert np.array_equal(r.result()[0], oracle.bfs(hg, s)[0])
     dobfs.graph_destroy(g)
+
+
+def test_shallow_queries_beside_deep_searches(graphs):
+    """Searches of thousands of levels keep their launches short enough that a small graph's query on
+    a stream that shares a hardware queue with them does not wait for a whole search: eight slots (a
+    process has four hardware queues), seven of them busy with a 2048 x 2048 grid. A batch of launches
+    holds a queue for about a millisecond and a search takes twelve, so the small graph's median
+    latency must stay below a quarter of the deep searches'."""
+    hg, g = graphs[0]
+    deep = gen.grid2d(2048, 2048)
+    gd = upload(deep)
+    srv = dobfs.Server([gd, g], slots=8, max_batch=1)
+    want = {s: oracle.bfs(deep, s)[0] for s in (0, deep.V // 2)}
+    want_small = oracle.bfs(hg, 1)[0]
+    rows = [_result_buffer(deep.V) for _ in range(15)]
+    small = _result_buffer(hg.V)
+    srv.wait(srv.submit(0, 0, rows[0]))  # the server knows the grid for a deep graph
+    srv.wait(srv.submit(1, 1, small))
+    src = [0 if k % 2 else deep.V // 2 for k in range(15)]
+    ids = [srv.submit(0, src[k], rows[k]) for k in range(15)]
+    time.sleep(0.002)
+    lat = []
+    while True:
+        info = srv.wait(srv.submit(1, 1, small))
+        lat.append(info["t_done_ms"] - info["t_submit_ms"])
+        try:
+            last = srv.wait(ids[-1], timeout_ms=0)
+            break
+        except dobfs.DobfsError as e:
+            assert e.status == dobfs.ERR_TIMEOUT
+    infos = [srv.wait(i) for i in ids[:-1]] + [last]
+    for k in range(15):
+        assert np.array_equal(rows[k].cpu().numpy(), want[src[k]]), k
+    assert np.array_equal(small.cpu().numpy(), want_small)
+    srv.close()
+    t_deep = float(np.median([x["t_done_ms"] - x["t_start_ms"] for x in infos]))
+    t_small = float(np.median(lat))
+    _say("deep %.1f ms, small %.2f ms over %d queries" % (t_deep, t_small, len(lat)))
+    assert t_small < t_deep / 4
+    dobfs.graph_destroy(gd)
