@@ -245,16 +245,14 @@ struct ReportSink {
   HostReport* host = nullptr;
 };
 
-hipError_t fetch_report(const ReportSink& r, uint32_t seq, hipStream_t s) {
+// max_rec: the most records it may have that are wanted. One copy and one wait.
+hipError_t fetch_report(const ReportSink& r, uint32_t seq, int32_t max_rec, hipStream_t s) {
   if (r.dev == r.host) return wait_report(r.host, seq, s);
-  hipError_t e = hipMemcpyAsync(r.host, r.dev, offsetof(HostReport, rec), hipMemcpyDeviceToHost, s);
+  const size_t bytes = offsetof(HostReport, rec) + sizeof(LevelRecord) * size_t(max_rec);
+  hipError_t e = hipMemcpyAsync(r.host, r.dev, bytes, hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return e;
-  if (r.host->seq != seq) return hipErrorUnknown;
-  if (r.host->nrec <= 0) return hipSuccess;
-  e = hipMemcpyAsync(r.host->rec, r.dev->rec, sizeof(LevelRecord) * size_t(r.host->nrec), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  return e;
+  return r.host->seq == seq ? hipSuccess : hipErrorUnknown;
 }
 
 // Per-thread, per-device events for the level loop's timers: the start and
@@ -580,8 +578,9 @@ struct SingleSteps {
   static int32_t capacity(const PersistentDevice& d) { return d.capacity; }
   hipError_t step(hipStream_t s, int32_t k, int64_t, bool narrow, hipEvent_t t0, hipEvent_t t1,
                   const StepReportArgs& rp) const {
-    return launch_step(s, a, k, t0, t1, rp, burst && (narrow || (k == 0 && a.max_outdeg <= kBurstDeg)));
+    return launch_step(s, a, k, t0, t1, rp, may_burst(narrow) && (narrow || k == 0));
   }
+  bool may_burst(bool narrow) const { return burst && (narrow || a.max_outdeg <= kBurstDeg); }
   // Whether launches are given the form that runs several narrow levels at once: the first launch
   // unless the graph has hubs that such a level cannot have (the second level is then wide as a
   // rule, and RMAT-22 lost 1% to the form that handles the first), the rest of the first batch on
@@ -640,8 +639,9 @@ struct BatchSteps {
   }
   hipError_t step(hipStream_t s, int32_t k, int64_t blocks, bool narrow, hipEvent_t t0, hipEvent_t t1,
                   const StepReportArgs& rp) const {
-    return launch_mb_step(s, a, k, blocks, burst && narrow, rp.level_end, t0, t1);
+    return launch_mb_step(s, a, k, blocks, may_burst(narrow), rp.level_end, t0, t1);
   }
+  bool may_burst(bool narrow) const { return burst && narrow; }
   // the depth rows: a transpose that exits at once unless the state the batch's last step
   // published says the traversal is over, so the last report already finds the rows final
   hipError_t before_report(hipStream_t s, int32_t k_last) const { return launch_mb_depth(s, a, k_last, rows); }
@@ -699,6 +699,7 @@ dobfs_status run_steps(LastRun& last, hipStream_t s, bool timing, hipEvent_t* ev
     // steps so that every step's end event has completed when the host reads it
     // a burst leaves it to single steps to reach the level that is too deep
     const bool records = stats || Steps::needs_records;
+    const int32_t max_rec = !records ? 0 : (bursts && S.may_burst(narrow)) ? kMaxRec : batch;
     const int32_t rec_from = records ? rec_first : INT32_MAX;
     const int32_t level_end =
         int32_t(std::min<int64_t>(rec_first + Steps::burst_levels, max_levels - 1));
@@ -712,14 +713,14 @@ dobfs_status run_steps(LastRun& last, hipStream_t s, bool timing, hipEvent_t* ev
                          self ? rp : no_report, E(ev_m0(0)), E(ev_m1(0))));
       HIPCK(S.before_report(s, int32_t(s0 + batch - 1)));
       if (!self) HIPCK(launch_step_report(s, ctrl, int32_t(s0), batch, rec_from, sink.dev, seq));
-      HIPCK(fetch_report(sink, seq, s));
+      HIPCK(fetch_report(sink, seq, max_rec, s));
     } else {
       for (int32_t k = 0; k < batch; ++k)
         HIPCK(S.step(s, int32_t(s0 + k), grid, narrow, E(ev_m0(k)), E(ev_m1(k)),
                      (self && k == batch - 1) ? rp : no_report));
       HIPCK(S.before_report(s, int32_t(s0 + batch - 1)));
       if (!self) HIPCK(launch_step_report(s, ctrl, int32_t(s0), batch, rec_from, sink.dev, seq));
-      HIPCK(fetch_report(sink, seq, s));
+      HIPCK(fetch_report(sink, seq, max_rec, s));
     }
     if (rep->error) {
       (void)hipStreamSynchronize(s);

@@ -3,6 +3,9 @@ dobfs_bfs on the same inputs: depths equal (and equal to the oracle's), parents 
 the pull-only mode (deterministic first-hit parents) parents equal too. Two calls in a row,
 the second on a smaller graph, share the device's static scratch; the call allocates no
 device memory; graphs beyond the scratch and options it cannot serve are refused."""
+import os
+import re
+import subprocess
 import sys
 
 import numpy as np
@@ -147,3 +150,36 @@ def test_static_limit(V, fits):
         assert e.value.status == dobfs.ERR_INVALID_ARG
         assert int(depth.max()) == -7
     dobfs.graph_destroy(g)
+
+
+_COUNT_WAITS = """
+import os, sys
+sys.path.insert(0, {root!r})
+import numpy as np, torch, gen
+from paper_1804_03327_amd import dobfs
+from paper_1804_03327_amd.helpers import upload
+hg = gen.rmat(10, 16, seed=1)
+g = upload(hg)
+d = torch.empty(g.V, dtype=torch.int32, device="cuda")
+st = dobfs.make_stats(64)
+dobfs.bfs_static(g, 1, d, stats=st)
+torch.cuda.synchronize()
+for stats in (st, None):
+    os.write(2, b"\\n== call\\n")
+    dobfs.bfs_static(g, 1, d, stats=stats)
+    os.write(2, b"\\n== end\\n")
+"""
+
+
+def test_static_waits_once_per_batch():
+    """A search that one batch of launches completes waits for the stream once, and once more for the
+    edge count where statistics are asked for, counted in the HIP runtime's own log of API calls."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    env = dict(os.environ, AMD_LOG_LEVEL="3", AMD_LOG_MASK="1")
+    r = subprocess.run([sys.executable, "-c", _COUNT_WAITS.format(root=root)], env=env, capture_output=True,
+                       text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    calls = [c.split("== end")[0] for c in r.stderr.split("== call")[1:]]
+    assert len(calls) == 2 and all("hipLaunchKernel" in c or "LaunchKernel" in c for c in calls), r.stderr[-2000:]
+    waits = [len(re.findall(r"hipStreamSynchronize \(", c)) for c in calls]
+    assert waits == [2, 1], waits
