@@ -9,6 +9,9 @@
 
 #include <hip/hip_ext.h>
 
+#define DOBFS_DEVICE __device__ __forceinline__
+#include "burst_join.h"
+
 namespace dobfs {
 namespace {
 
@@ -727,8 +730,6 @@ struct ListMap {
 // ------------------------------------------------- bursts: what both kinds share
 constexpr uint32_t kBurstEdges = 1024;       // most out-edges of a burst level, per member
 constexpr uint32_t kBurstEven = 64;          // parts up to this size are not evened out (256: grid levels 15% slower)
-constexpr uint32_t kBurstJoinPolls = 16;     // the leader's wait for the candidates (about 4 us)
-constexpr uint32_t kBurstSpin = 1u << 22;    // bound of every other wait (polls)
 
 // Who takes part in a burst, in LDS: how many members, this block's place among them (-1: none),
 // whether every wait has ended well, and where the list's append counter stood.
@@ -751,6 +752,21 @@ __device__ __forceinline__ void agent_store(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The words a step's burst meets in (burst_join.h).
+struct BurstWords {
+  uint32_t* joined;
+  unsigned long long* members;
+  __device__ __forceinline__ uint32_t load_joined() const { return agent_load(joined); }
+  __device__ __forceinline__ uint32_t or_joined(uint32_t v) const {
+    return __hip_atomic_fetch_or(joined, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ uint32_t add_joined() const {
+    return __hip_atomic_fetch_add(joined, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ unsigned long long load_members() const { return agent_load(members); }
+  __device__ __forceinline__ void store_members(unsigned long long v) const { agent_store(members, v); }
+};
+
 // The size of a part of a frontier, in threads of kExpandEPT edges: what a member's rounds go by.
 __device__ __forceinline__ uint32_t burst_part(uint32_t vertices, uint32_t edges) {
   return max(vertices, edges / uint32_t(kExpandEPT));
@@ -769,8 +785,7 @@ __device__ __forceinline__ int burst_map_shift(uint32_t maxdeg, int32_t nc) {
 __device__ __forceinline__ bool burst_join(Ctrl* c, int32_t s, uint32_t most, BurstTeam& t) {
   if (threadIdx.x == 0) {
     BurstCtl& b = c->burst;
-    uint32_t* joined = &b.joined[s % kSlots][0];
-    unsigned long long* members = &b.members[s % kSlots][0];
+    BurstWords m{&b.joined[s % kSlots][0], &b.members[s % kSlots][0]};
     t.rank = -1;
     t.ok = 1;
     if (most == 1) {
@@ -778,24 +793,19 @@ __device__ __forceinline__ bool burst_join(Ctrl* c, int32_t s, uint32_t most, Bu
       t.rank = 0;
       t.head = agent_load(&b.head);
     } else if (blockIdx.x == 0) {
-      for (uint32_t p = 0; p < kBurstJoinPolls && agent_load(joined) < uint32_t(kBurstBlocks - 1); ++p) {}
-      const uint32_t got = __hip_atomic_fetch_or(joined, kBurstClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      t.n = int32_t(min(got, uint32_t(kBurstBlocks - 1))) + 1;
+      t.n = int32_t(burst_lead(m, uint32_t(kBurstBlocks - 1))) + 1;
       t.rank = 0;
       t.head = agent_load(&b.head);
       agent_store(&b.head2, 0u);
       __builtin_amdgcn_s_waitcnt(0);
-      agent_store(members, (unsigned long long)uint32_t(t.n) | ((unsigned long long)t.head << 32));
+      m.store_members((unsigned long long)uint32_t(t.n) | ((unsigned long long)t.head << 32));
     } else {
-      const uint32_t at = __hip_atomic_fetch_add(joined, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (!(at & kBurstClosed)) {
-        unsigned long long m = 0;
-        for (uint32_t p = 0; p < kBurstSpin && m == 0; ++p) m = agent_load(members);
-        t.n = int32_t(uint32_t(m));
-        t.head = uint32_t(m >> 32);
-        t.rank = m ? int32_t(at) + 1 : -1;
-        if (!m) __hip_atomic_fetch_or(&c->bar.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      unsigned long long told;
+      const int32_t at = burst_follow(m, &told);
+      t.n = int32_t(uint32_t(told));
+      t.head = uint32_t(told >> 32);
+      t.rank = told ? at + 1 : -1;
+      if (at >= 0 && !told) __hip_atomic_fetch_or(&c->bar.abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
   __syncthreads();

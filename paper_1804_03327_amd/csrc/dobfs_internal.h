@@ -90,7 +90,7 @@ struct GridBar {
 };
 
 // A burst: consecutive narrow levels run by a few blocks of one step launch (burst_run). Blocks
-// join in slot s % kSlots of step s; the leader closes the slot and publishes how many joined and
+// join in slot s % kSlots of step s (burst_join.h); the leader publishes how many joined and
 // where the append counter `head` stands (the counter only grows within a traversal). Members
 // leave their totals in rec, every word with a tag that grows through the traversal in its upper
 // half, and wait for everybody's: the exchange of the totals is the barrier.
@@ -100,7 +100,7 @@ constexpr int kMbBurstWords = 16;
 constexpr uint32_t kBurstNf = 256;    // most frontier vertices of a burst level, per member
 constexpr uint32_t kBurstDeg = 1024;  // largest out-degree (a row is one member's)
 struct BurstCtl {
-  alignas(128) uint32_t joined[kSlots][32];          // a line per slot; kBurstClosed: too late
+  alignas(128) uint32_t joined[kSlots][32];             // a line per slot (burst_join.h)
   alignas(128) unsigned long long members[kSlots][16];  // members | head << 32; 0: not yet known
   alignas(128) uint32_t head;
   alignas(128) unsigned long long rec[2][kBurstBlocks][kBurstWords];
@@ -110,7 +110,6 @@ struct BurstCtl {
   alignas(128) unsigned long long mb_rec[2][kBurstBlocks][kMbBurstWords];
   alignas(128) unsigned long long bar[2][kBurstBlocks];
 };
-constexpr uint32_t kBurstClosed = 1u << 31;
 
 // The list a push of the step loops leaves, in up to kListSegs segments, each with an append
 // counter on a line of its own: segment j starts at j * list_seg_cap(V). Several are used only by

@@ -1160,9 +1160,10 @@ __device__ __forceinline__ void step_body(const BfsArgs& a, const LevelState& st
 // the next level's neighbours and their visited words; only the claims have to wait. The frontier
 // goes through the list in memory when one member's part outgrows the others', and at the end.
 //
-// Who takes part is settled at run time: the candidates join, the leader (block 0) waits for them a
-// few microseconds at most and closes the list, so every wait in a burst is for a block that is
-// running, whatever else occupies the device. Nothing but speed depends on where the members run:
+// Who takes part is settled at run time (burst_join.h): the leader (block 0) opens a list, waits for
+// the candidates a few microseconds and closes it; a candidate that finds it not open leaves after a
+// bounded wait. So whoever has joined only waits for blocks that are running, whatever else occupies
+// the device and in whatever order blocks start. Nothing but speed depends on where the members run:
 // all they pass to each other (list, claims, totals) is written and read by agent-scope atomics,
 // and a member publishes its totals only after what the others may read has completed. The visited
 // word an edge looks at before its claim may be stale; a stale word costs a claim that fails.
@@ -1542,7 +1543,7 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
   // this launch's results are final only when the launch is over. The step after it finds the end.
   if (r == 0 && rp.host) {
     __syncthreads();
-    step_report(c, rp, s, st, st, LevelTotals{0, 0, 0, 0, 0, 0}, false, failed ? 1 : 0);
+    step_report(c, rp, s, st, st, LevelTotals{0, 0, 0, 0, 0, 0}, false, failed || agent_load(&c->bar.abort) ? 1 : 0);
   }
 }
 
