@@ -631,11 +631,12 @@ struct BatchSteps {
     return g < grid() ? g : 0;
   }
   static int32_t capacity(const PersistentDevice& d) { return d.capacity_mb; }
-  // launches that may run several narrow levels: on graphs of low degree, as in SingleSteps
-  bool narrow_first() const { return a.low_degree != 0; }
+  // launches that may run several narrow levels: on graphs of low degree, as in SingleSteps, and
+  // where such levels may come (the form costs the others: 20% on a tree of 7.2 million vertices)
+  bool narrow_first() const { return a.low_degree != 0 && mb_burst_level(a.V, 0); }
   bool narrow_next(const HostReport& r) const {
     const LevelState& st = r.end;
-    return st.dir == DOBFS_DIR_PUSH && uint32_t(st.nf) <= kBurstNf * kBurstBlocks;
+    return st.dir == DOBFS_DIR_PUSH && uint32_t(st.nf) <= kBurstNf * kBurstBlocks && mb_burst_level(a.V, st.level + 1);
   }
   hipError_t step(hipStream_t s, int32_t k, int64_t blocks, bool narrow, hipEvent_t t0, hipEvent_t t1,
                   const StepReportArgs& rp) const {

@@ -830,9 +830,9 @@ struct MbEdges {
 };
 
 // Whether level st, of at most mf out-edges, is one for n members.
-__device__ __forceinline__ bool mb_burst_fits(const LevelState& st, uint64_t mf, uint32_t n) {
+__device__ __forceinline__ bool mb_burst_fits(const BatchArgs& a, const LevelState& st, uint64_t mf, uint32_t n) {
   return !st.done && st.dir == 0 && st.phase == kPhaseScan && st.list_valid && uint32_t(st.nf) <= kBurstNf * n &&
-         mf <= uint64_t(kBurstEdges) * n;
+         mf <= uint64_t(kBurstEdges) * n && mb_burst_level(a.V, st.level);
 }
 
 __device__ __forceinline__ unsigned long long agent_load64(const uint64_t* p) {
@@ -1173,7 +1173,7 @@ __device__ __forceinline__ void mb_burst_run(const BatchArgs& a, LevelState st, 
     m_f = t.v[kMbMnew];
     const int32_t forced = L + 1 < a.n_forced ? int32_t(c->forced[L + 1]) : -1;
     const LevelState next = mb_burst_next(a, forced, st, t);
-    const bool go_on = mb_burst_fits(next, t.v[kMbMnew], n) && L + 1 < level_end;
+    const bool go_on = mb_burst_fits(a, next, t.v[kMbMnew], n) && L + 1 < level_end;
     if (r == 0 && tid == 0) {
       if (go_on || next.done) {
         LevelRecord rec;
@@ -1309,7 +1309,7 @@ __global__ __launch_bounds__(kThreads) void k_mb_step(BatchArgs a, int32_t s, in
   if (st.done) return;
   if (kBurst) {
     const uint64_t bound = s > 0 && a.edge_rule ? tot.mnew : uint64_t(st.nf) * a.max_outdeg;
-    if (mb_burst_fits(st, bound, kBurstBlocks)) {
+    if (mb_burst_fits(a, st, bound, kBurstBlocks)) {
       if (blockIdx.x % 8 == 0 && blockIdx.x < 8 * kBurstBlocks) mb_burst_run(a, st, prev, s, level_end, sh.b);
       return;
     }

@@ -413,6 +413,16 @@ __host__ __device__ inline int32_t mb_frontier_slot(int32_t L) { return L < kMbS
 __host__ __device__ inline int64_t mb_fstride(int64_t V) { return (V + 31) / 32 * 32; }
 // whether level L's frontier buffer held the frontier of level L - 2 in this traversal
 __host__ __device__ inline bool mb_frontier_recycled(int32_t L) { return L >= kMbSnap + 2; }
+// Whether level L of a traversal of V vertices may be run by a burst. The first levels' buffers are
+// made zero whole, one a level: a step does it on the whole chip, a burst's members alone at
+// 0.36 TB/s (64 MB in 180 us), so on large graphs those levels are not for a burst. At half a million
+// vertices it costs 11 us, about what the burst saves of the level's two launches; at a million
+// bursts gained nothing, and at 7.2 million (a tree of 15 levels) the call took 3.06 instead of
+// 2.36 ms.
+constexpr int32_t kMbBurstZeroV = 1 << 19;
+__host__ __device__ inline bool mb_burst_level(int32_t V, int32_t L) {
+  return V <= kMbBurstZeroV || mb_frontier_recycled(L + 1);
+}
 // A multi-source push over more edges than this marks its winners in the
 // next frontier's non-zero bitmap (non-returning atomics) instead of listing
 // them: every block reserving list space with one returning atomic on a single

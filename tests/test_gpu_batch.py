@@ -6,6 +6,7 @@ bit, in every supported mode and under forced push/pull schedules. Per-level sta
 checked against what the oracle's depth rows fix: the vertices carrying any frontier bit at
 each level, the (vertex, source) pairs reached, and the level count."""
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -437,4 +438,33 @@ def test_batch_narrow_levels_in_one_launch(d, k):
                 assert row["edges"] == row["m_f"] == want, "%s level %d" % (tag, L)
         d2, _ = _run(g, srcs, opt)
         assert np.array_equal(d2, d_), tag
+    dobfs.graph_destroy(g)
+
+
+def test_batch_first_levels_of_a_large_tree():
+    """The first levels' frontier buffers are made zero whole, work for the whole chip. Timed calls
+    run a step per launch and record two events with each, untimed ones may run several narrow levels
+    in a launch and do less on the host: on a ternary tree of 7 million vertices (15 levels, 57 MB a
+    buffer) they must not take longer."""
+    V = (3 ** 15 - 1) // 2
+    child = np.arange(1, V)
+    hg = gen.from_edges(V, (child - 1) // 3, child, directed=False, name="ternary14")
+    g = upload(hg)
+    srcs = [0, V - 1]
+    want = np.stack([oracle.bfs(hg, s)[0] for s in srcs])
+    depth = torch.empty(2 * V, dtype=torch.int32, device="cuda")
+    ws = torch.empty(dobfs.bfs_batch_workspace_bytes(g, 2), dtype=torch.uint8, device="cuda")
+    ms = {}
+    for timed in (False, True, False, True):
+        opt = dobfs.make_options("full", time_kernels=timed)
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            dobfs.bfs_batch(g, srcs, depth, opt, ws)
+            torch.cuda.synchronize()
+            t = 1e3 * (time.perf_counter() - t0)
+            ms[timed] = min(ms.get(timed, t), t)
+        assert np.array_equal(depth.cpu().numpy().reshape(2, V), want)
+    _say(hg.name, "untimed %.2f ms, timed %.2f ms" % (ms[False], ms[True]))
+    assert ms[False] < ms[True]
     dobfs.graph_destroy(g)
