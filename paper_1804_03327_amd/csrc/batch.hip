@@ -1055,16 +1055,20 @@ __device__ __forceinline__ void mb_burst_zero(const BatchArgs& a, uint64_t* F, u
   for (int64_t i = int64_t(r) * kThreads + threadIdx.x; i < a.V; i += int64_t(n) * kThreads) agent_store64(&F[i], 0ull);
 }
 
-// Step s from its level st on (candidate blocks; prev: the state of the level before): levels while
+// Step s from its level st on (candidate blocks; prev: the state of the level before; mf: most
+// out-edges of st): levels while
 // they fit and stay below level_end. Block 0 leaves what the two steps of the last of them would
 // leave, or, when the traversal ended, the final state.
 __device__ __forceinline__ void mb_burst_run(const BatchArgs& a, LevelState st, const LevelState& prev, int32_t s,
-                                             int32_t level_end, MbBurstShared& sh) {
+                                             uint64_t mf, int32_t level_end, MbBurstShared& sh) {
   Ctrl* c = a.ctrl;
   const int tid = threadIdx.x;
   for (int i = tid; i < 2 * kMbBurstWords; i += kThreads) (&sh.red[0][0])[i] = 0;
   if (tid < 2) sh.nbuf[tid] = 0;
-  if (!burst_join(c, s, kBurstBlocks, sh.team)) return;
+  // a whole buffer made zero counts as kBurstEdges edges for a member's every 128 KB
+  const bool zeroes = st.level >= 1 && !mb_frontier_recycled(st.level + 1);
+  const uint32_t zero = zeroes ? uint32_t(a.V) / (kMbBurstZeroV / kBurstBlocks) * kBurstEdges : 0u;
+  if (!burst_join(c, s, kBurstBlocks, uint32_t(st.nf), max(uint32_t(mf), zero), sh.team)) return;
   const uint32_t n = uint32_t(sh.team.n), r = uint32_t(sh.team.rank);
   uint64_t* vis = a.vis[st.vis_idx];
   uint32_t base = sh.team.head;
@@ -1310,7 +1314,7 @@ __global__ __launch_bounds__(kThreads) void k_mb_step(BatchArgs a, int32_t s, in
   if (kBurst) {
     const uint64_t bound = s > 0 && a.edge_rule ? tot.mnew : uint64_t(st.nf) * a.max_outdeg;
     if (mb_burst_fits(a, st, bound, kBurstBlocks)) {
-      if (blockIdx.x % 8 == 0 && blockIdx.x < 8 * kBurstBlocks) mb_burst_run(a, st, prev, s, level_end, sh.b);
+      if (blockIdx.x % 8 == 0 && blockIdx.x < 8 * kBurstBlocks) mb_burst_run(a, st, prev, s, bound, level_end, sh.b);
       return;
     }
   }

@@ -18,14 +18,19 @@ namespace dobfs {
 
 constexpr uint32_t kBurstClosed = 1u << 31, kBurstOpen = 1u << 30, kBurstCount = kBurstOpen - 1u;
 constexpr uint32_t kBurstJoinPolls = 16;   // the leader's wait for the candidates (about 4 us)
+constexpr uint32_t kBurstWantPolls = 256;  // its wait while they are too few for the level (about 60 us)
 constexpr uint32_t kBurstOpenPolls = 256;  // a candidate's wait for the leader (about 60 us)
 constexpr uint32_t kBurstSpin = 1u << 22;  // bound of the waits for blocks that run (polls)
 
-// The leader: opens, waits and closes. Returns how many candidates joined, at most `most`.
+// The leader: opens, waits and closes. want: how many the first level has a round of work for (the
+// blocks that stay out have left by then, so a full-size level would be left to a few: 32 rounds for
+// one member). Returns how many candidates joined, at most `most`.
 template <class M>
-DOBFS_DEVICE uint32_t burst_lead(M& m, uint32_t most) {
+DOBFS_DEVICE uint32_t burst_lead(M& m, uint32_t most, uint32_t want) {
   m.or_joined(kBurstOpen);
-  for (uint32_t p = 0; p < kBurstJoinPolls && (m.load_joined() & kBurstCount) < most; ++p) {}
+  uint32_t seen = 0;
+  for (uint32_t p = 0; seen < most && p < (seen < want ? kBurstWantPolls : kBurstJoinPolls); ++p)
+    seen = m.load_joined() & kBurstCount;
   const uint32_t got = m.or_joined(kBurstClosed) & kBurstCount;
   return got < most ? got : most;
 }

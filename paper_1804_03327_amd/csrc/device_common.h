@@ -781,8 +781,9 @@ __device__ __forceinline__ int burst_map_shift(uint32_t maxdeg, int32_t nc) {
   return nc <= kThreads && maxdeg <= (uint32_t(kExpandEPT) << shift) ? shift : -1;
 }
 
-// Joins step s's burst, one for `most` members (all threads of a candidate block). False: too late.
-__device__ __forceinline__ bool burst_join(Ctrl* c, int32_t s, uint32_t most, BurstTeam& t) {
+// Joins step s's burst, one for `most` members, whose first level has nf vertices and at most mf
+// out-edges (all threads of a candidate block). False: too late.
+__device__ __forceinline__ bool burst_join(Ctrl* c, int32_t s, uint32_t most, uint32_t nf, uint32_t mf, BurstTeam& t) {
   if (threadIdx.x == 0) {
     BurstCtl& b = c->burst;
     BurstWords m{&b.joined[s % kSlots][0], &b.members[s % kSlots][0]};
@@ -793,7 +794,8 @@ __device__ __forceinline__ bool burst_join(Ctrl* c, int32_t s, uint32_t most, Bu
       t.rank = 0;
       t.head = agent_load(&b.head);
     } else if (blockIdx.x == 0) {
-      t.n = int32_t(burst_lead(m, uint32_t(kBurstBlocks - 1))) + 1;
+      const uint32_t want = (max(nf / kBurstNf, mf / kBurstEdges) * 3u) / 4u;  // three quarters: two rounds at most
+      t.n = int32_t(burst_lead(m, uint32_t(kBurstBlocks - 1), want)) + 1;
       t.rank = 0;
       t.head = agent_load(&b.head);
       agent_store(&b.head2, 0u);

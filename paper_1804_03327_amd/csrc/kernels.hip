@@ -1410,7 +1410,7 @@ __device__ __forceinline__ void burst_run(const BfsArgs& a, LevelState st, int32
   Ctrl* c = a.ctrl;
   if (threadIdx.x < 2 * kBurstWords) (&sh.red[0][0])[threadIdx.x] = 0;
   if (threadIdx.x < 2) sh.nbuf[threadIdx.x] = 0;
-  if (!burst_join(c, s, burst_members(a), sh.team)) return;
+  if (!burst_join(c, s, burst_members(a), uint32_t(st.nf), uint32_t(st.active >> 32), sh.team)) return;
   const int tid = threadIdx.x;
   const uint32_t n = uint32_t(sh.team.n), r = uint32_t(sh.team.rank);
   uint32_t* claim = a.vis[st.vis_idx];

@@ -43,13 +43,27 @@ int no_leader() {  // candidates whose leader has not started leave, soon and wi
     CHECK(w.polls < 1000);
   }
   CHECK((w.joined & kBurstCount) == 0);
-  CHECK(burst_lead(w, 31) == 0);  // and it goes on without them
+  w.polls = 0;
+  CHECK(burst_lead(w, 31, 0) == 0);  // and it goes on without them
+  CHECK(w.polls < 100);
+  return 0;
+}
+
+int few() {  // a leader with a full-size level waits for candidates that come late, not for good
+  Words w;
+  w.tick = [](Words& x) { if (x.polls % 10 == 0 && (x.joined & kBurstOpen)) x.joined.fetch_add(1); };
+  CHECK(burst_lead(w, 31, 16) >= 16);
+  Words v;
+  v.tick = [](Words& x) { if (x.polls % 10 == 0 && (x.joined & kBurstOpen)) x.joined.fetch_add(1); };
+  CHECK(burst_lead(v, 31, 2) < 8 && v.polls < 100);
+  Words none;
+  CHECK(burst_lead(none, 31, 16) == 0 && none.polls < 1000);
   return 0;
 }
 
 int too_late() {
   Words w;
-  CHECK(burst_lead(w, 31) == 0);
+  CHECK(burst_lead(w, 31, 0) == 0);
   w.store_members(1);
   unsigned long long told;
   CHECK(burst_follow(w, &told) == -1 && told == 0);
@@ -69,7 +83,7 @@ int threads(int candidates, int spread) {  // whoever joins has a place of its o
     });
     t.emplace_back([&] {
       for (int i = 0; i < round % 3; ++i) std::this_thread::yield();
-      n = burst_lead(w, uint32_t(candidates));
+      n = burst_lead(w, uint32_t(candidates), uint32_t(round % (candidates + 1)));
       w.store_members(n + 1);
     });
     for (auto& x : t) x.join();
@@ -88,6 +102,7 @@ int threads(int candidates, int spread) {  // whoever joins has a place of its o
 int main(int, char** argv) {
   if (!std::strcmp(argv[1], "no_leader")) return no_leader();
   if (!std::strcmp(argv[1], "too_late")) return too_late();
+  if (!std::strcmp(argv[1], "few")) return few();
   if (!std::strcmp(argv[1], "threads")) return threads(7, 0) || threads(7, 3);
   return 2;
 }
@@ -102,7 +117,7 @@ def harness(tmp_path_factory):
     return str(d / "h")
 
 
-@pytest.mark.parametrize("case", ["no_leader", "too_late", "threads"])
+@pytest.mark.parametrize("case", ["no_leader", "too_late", "few", "threads"])
 def test_burst_join(harness, case):
     r = subprocess.run([harness, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
