@@ -23,6 +23,8 @@
 
 #include "device_common.h"
 
+#include <type_traits>
+
 namespace dobfs {
 namespace {
 
@@ -465,13 +467,14 @@ __device__ __forceinline__ void mb_pull_body(const BatchArgs& a, const LevelStat
 // vertices has the hubs, so that rows are completed early after all: 11 613 vertices, 4 sources
 // 118 us per launch without this limit, 112 with it, 114 with rows only; 65 521 vertices, 13
 // sources, 134 with it and 137 with rows only. (An eighth: 4% behind rows on a directed graph of
-// 20 000 vertices.)
+// 20 000 vertices.) Not on graphs of low degree: a row there is read in a round or two either way,
+// and a list that makes the rule turn to pulls is longer.
 constexpr int kMbSparseNf = 8192;
 constexpr int kMbFilterBits = 17;
 constexpr int kMbSparseU = 4;                   // entries a lane reads at once
 constexpr int kMbSparseWin = 64 * kMbSparseU;   // entries of a wave's window
 __device__ __forceinline__ bool mb_sparse_level(const BatchArgs& a, const LevelState& st) {
-  return st.local == 1 && st.list_valid && st.nf <= min(kMbSparseNf, a.V / 64);
+  return !a.low_degree && st.local == 1 && st.list_valid && st.nf <= min(kMbSparseNf, a.V / 64);
 }
 
 struct MbSparseShared {
@@ -1268,50 +1271,66 @@ __device__ __forceinline__ void mb_burst_run(const BatchArgs& a, LevelState st, 
   }
 }
 
-union MbShared {
+union MbPlainShared {
   MbExpandShared e;
   MbPullShared p;
+};
+union MbShared {
+  MbPlainShared plain;
   MbSparseShared f;
   MbBurstShared b;
 };
 
-// The work of step s (state st, prev: the state before it) over the launch's grid.
-__device__ __forceinline__ void mb_step_body(const BatchArgs& a, const LevelState& st, const LevelState& prev,
-                                             int32_t s, MbShared& sh) {
+// The work of step s (state st, prev: the state before it) over the launch's grid, without the pull
+// that reads a filter.
+__device__ __forceinline__ void mb_plain_body(const BatchArgs& a, const LevelState& st, const LevelState& prev,
+                                              int32_t s, MbPlainShared& sh) {
   if (st.phase == kPhaseScan) {
     mb_scan_step(a, st, prev, s);
   } else if (st.dir == 0) {
     mb_expand_body(a, st, s, sh.e);
   } else {
     const int32_t ntiles = (a.nwords + kMbTileWords - 1) / kMbTileWords;
-    if (mb_sparse_level(a, st)) {
-      if (int32_t(blockIdx.x) >= ntiles) return;
-      mb_filter_build(a, st, sh.f);
-      for (int32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        mb_pull_sparse(a, st, s, t, sh.f);
-        __syncthreads();  // LDS of this tile is no longer read
-      }
-      return;
-    }
     for (int32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
       __syncthreads();  // LDS of the previous tile is no longer read
       mb_pull_body(a, st, s, t, sh.p);
     }
   }
 }
+__device__ __forceinline__ void mb_step_body(const BatchArgs& a, const LevelState& st, const LevelState& prev,
+                                             int32_t s, MbShared& sh) {
+  if (st.phase != kPhaseScan && st.dir != 0 && mb_sparse_level(a, st)) {
+    const int32_t ntiles = (a.nwords + kMbTileWords - 1) / kMbTileWords;
+    if (int32_t(blockIdx.x) >= ntiles) return;
+    mb_filter_build(a, st, sh.f);
+    for (int32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+      mb_pull_sparse(a, st, s, t, sh.f);
+      __syncthreads();  // LDS of this tile is no longer read
+    }
+    return;
+  }
+  mb_plain_body(a, st, prev, s, sh.plain);
+}
+__device__ __forceinline__ void mb_step_body(const BatchArgs& a, const LevelState& st, const LevelState& prev,
+                                             int32_t s, MbPlainShared& sh) {
+  mb_plain_body(a, st, prev, s, sh);
+}
 
 // kBurst: the form that may run several narrow levels, launched where they are expected
-// (BatchSteps); either form is right for any level.
-template <bool kBurst>
+// (BatchSteps). kSparse: with the pull that reads a filter; its registers and LDS leave room for 6
+// blocks per CU instead of 7, so graphs that never use it (mb_sparse_level) run without: 8 sources
+// on a 200^3 lattice 54.4 ms instead of 60.0, on a tree of 7.2 million vertices 2.20 instead of 2.30.
+template <bool kBurst, bool kSparse>
 __global__ __launch_bounds__(kThreads) void k_mb_step(BatchArgs a, int32_t s, int32_t level_end) {
-  __shared__ MbShared sh;
+  static_assert(kSparse || !kBurst, "a burst's LDS is as large");
+  __shared__ std::conditional_t<kSparse, MbShared, MbPlainShared> sh;
   LevelTotals tot;
   LevelState prev;
   bool new_level;
   const LevelState st = mb_step_state(a, s, &tot, &prev, &new_level);
   if (blockIdx.x == 0) publish_step(a.ctrl, s, st, prev, tot, new_level);
   if (st.done) return;
-  if (kBurst) {
+  if constexpr (kBurst) {
     const uint64_t bound = s > 0 && a.edge_rule ? tot.mnew : uint64_t(st.nf) * a.max_outdeg;
     if (mb_burst_fits(a, st, bound, kBurstBlocks)) {
       if (blockIdx.x % 8 == 0 && blockIdx.x < 8 * kBurstBlocks) mb_burst_run(a, st, prev, s, bound, level_end, sh.b);
@@ -1489,8 +1508,9 @@ hipError_t launch_mb_step(hipStream_t s, const BatchArgs& a, int32_t step, int64
   const int64_t tiles = (int64_t(a.nwords) + kMbTileWords - 1) / kMbTileWords;
   const int64_t full = std::max<int64_t>(kExpandBlocks, std::min<int64_t>(tiles, 8192));
   const dim3 g(unsigned(blocks > 0 && blocks < full ? blocks : full));
-  if (burst) return launch_k(k_mb_step<true>, g, s, t0, t1, a, step, level_end);
-  return launch_k(k_mb_step<false>, g, s, t0, t1, a, step, level_end);
+  if (burst) return launch_k(k_mb_step<true, true>, g, s, t0, t1, a, step, level_end);
+  if (a.low_degree) return launch_k(k_mb_step<false, false>, g, s, t0, t1, a, step, level_end);
+  return launch_k(k_mb_step<false, true>, g, s, t0, t1, a, step, level_end);
 }
 
 hipError_t launch_mb_steps(hipStream_t s, const BatchArgs& a, int32_t s_first, int32_t n, int32_t blocks,

@@ -468,3 +468,18 @@ def test_batch_first_levels_of_a_large_tree():
     _say(hg.name, "untimed %.2f ms, timed %.2f ms" % (ms[False], ms[True]))
     assert ms[False] < ms[True]
     dobfs.graph_destroy(g)
+
+
+def test_batch_low_degree_pull_checks(graphs):
+    """On graphs of low degree a pull after a short list reads rows one by one: it checks no
+    in-neighbour of a row that has what it wants, and stops where a row is complete."""
+    for name in ("grid61x53", "lattice37"):
+        hg, g = graphs[name]
+        s = hg.V // 2
+        d, st = _run(g, [s], dobfs.make_options("full", forced_dirs=[PUSH, PULL]))
+        _check(hg, [s], d, st, name)
+        indeg = hg.in_degree()
+        open_rows = int(indeg[(d[0] > 1) | (d[0] < 0)].sum())
+        found = int(indeg[d[0] == 2].sum())
+        lv = dobfs.stats_levels(st)
+        assert open_rows - found + int((d[0] == 2).sum()) <= lv[1]["edges"] <= open_rows, name
