@@ -967,6 +967,7 @@ dobfs_status bfs_steps(dobfs_graph g, int32_t source, const dobfs_options& opt, 
   if (opt.flags & DOBFS_OPT_PERSISTENT) {
     pd = persistent_device(g->device);
     if (!pd) return fail(DOBFS_ERR_UNSUPPORTED, "the persistent level loop is not available on device %d", g->device);
+    a.pull_words = pull_tile_words(a.nwords, pd->capacity);
   }
   dobfs_status st = run_steps(g->last, s, timing, ev, SingleSteps{a, a.local_push && !timing}, a.ctrl, max_steps,
                               INT64_MAX, DOBFS_ERR_INTERNAL, sink, pd, stats, &res);
