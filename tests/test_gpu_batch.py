@@ -483,3 +483,40 @@ def test_batch_low_degree_pull_checks(graphs):
         found = int(indeg[d[0] == 2].sum())
         lv = dobfs.stats_levels(st)
         assert open_rows - found + int((d[0] == 2).sum()) <= lv[1]["edges"] <= open_rows, name
+
+
+@pytest.mark.parametrize("pre", [0, 1, 257, 1023])
+@pytest.mark.parametrize("n", [8193, 9215, 9216, 9217, 9471, 9472, 9473, 10_239, 10_240, 10_241, 20_000])
+def test_batch_filtered_pull_through_a_hub(n, pre):
+    """The filtered pull over a tile with a hub's row of n in-neighbours, past the 8192 entries from
+    which windows that lie inside one row are read in pairs: pre entries of other rows shift the row
+    against the windows, and n puts its end around theirs. Each of 63 sources reaches one in-neighbour
+    of the hub, at the windows' and the row's edges and between, the 64th none, so an entry that is
+    skipped or read twice for another row shows in that source's depths; every in-neighbour is
+    checked once."""
+    rng = np.random.default_rng(n + pre)
+    hub, x0 = 100, 256
+    pos = [0, 1, 255, 256, 257, 1023, 1024, 1025, 1279, 1280, 2047, 2048, 2303, 2304]
+    pos += [q - pre for q in (256, 1024, 1280, 2048, 2304, 4096, 8192) if q >= pre]
+    pos += [n - q for q in (1, 2, 255, 256, 257, 1023, 1024, 1025, 1279, 1280, 1281, 2047, 2048, 2049, 2304)]
+    pos = sorted({q for q in pos if 0 <= q < n})
+    rest = np.setdiff1d(np.arange(n), pos)
+    pos = (pos + [int(q) for q in rng.permutation(rest)])[:63]
+    assert len(pos) == 63
+    s0 = x0 + n  # the sources, then what they reach besides, a vertex of many out-edges and its leaves
+    other, fan, V = s0 + 64, s0 + 65, s0 + 65 + 1 + 40
+    src = [np.arange(x0, x0 + n), s0 + np.arange(63), [s0 + 63], np.full(40, fan), [hub, hub],
+           x0 + rng.choice(n, pre, replace=False), x0 + rng.choice(n, 300, replace=False)]
+    dst = [np.full(n, hub), x0 + np.array(pos), [other], fan + 1 + np.arange(40), [other, 255],
+           np.arange(pre) % hub, hub + 1 + np.arange(300) % 154]
+    hg = gen.from_edges(V, np.concatenate(src), np.concatenate(dst), directed=True, name="hubrow%d_%d" % (n, pre))
+    g = upload(hg)
+    srcs = [s0 + b for b in range(64)]
+    for sc in ([PUSH, PULL, PULL, PULL], [PUSH, PULL, PUSH, PUSH]):
+        d, st = _run(g, srcs, dobfs.make_options("full", forced_dirs=sc))
+        _check(hg, srcs, d, st, "%s %s" % (hg.name, sc))
+        assert dobfs.stats_levels(st)[1]["edges"] == hg.nnz, hg.name
+    one = [srcs[0]]  # most rows of the hub's tile miss the only source too
+    d, st = _run(g, one, dobfs.make_options("full", forced_dirs=[PUSH, PULL]))
+    _check(hg, one, d, st, hg.name)
+    dobfs.graph_destroy(g)
