@@ -42,16 +42,17 @@ def log(*a):
 
 
 # the sources the single-source kernels (k_bfs_init, k_step) are compiled from: kernels.hip and
-# the headers it includes (the multi-source, sort and host files do not change them); the
-# multi-source kernels likewise come from batch.hip and the same headers
-SINGLE_SOURCE_KERNEL_FILES = ("kernels.hip", "device_common.h", "dobfs_internal.h", "dobfs.h")
-MULTI_SOURCE_KERNEL_FILES = ("batch.hip", "device_common.h", "dobfs_internal.h", "dobfs.h")
+# the headers (the multi-source, sort and host files do not change them); the multi-source
+# kernels likewise come from batch.hip and the same headers
+SINGLE_SOURCE_KERNEL_FILES = ("kernels.hip", "dobfs.h")
+MULTI_SOURCE_KERNEL_FILES = ("batch.hip", "dobfs.h")
 
 
 def kernel_source_hash(files=SINGLE_SOURCE_KERNEL_FILES) -> str:
-    """SHA-256 (16 hex digits) over the sources of a group of kernels."""
+    """SHA-256 (16 hex digits) over the sources of a group of kernels: the given files and every
+    header beside them."""
     h = hashlib.sha256()
-    for name in files:
+    for name in (*files, *sorted(n for n in os.listdir(KERNEL_DIR) if n.endswith(".h"))):
         path = os.path.join(KERNEL_DIR, name)
         if not os.path.exists(path):
             path = os.path.join(ROOT, "include", name)

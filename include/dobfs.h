@@ -168,10 +168,13 @@ typedef struct {
                                 tile (4096 rows, fewer on graphs below 4 M vertices) found more
                                 rows than this, 0 .. 4096 (default 512) */
   int32_t local_unit;        /* block-local push: frontier vertices a block takes at once,
-                                1 .. 256 (default 128) */
+                                1 .. 256 (default 128). On graphs with no row above 8 entries
+                                it matters to the push after a pull only: over a list, two
+                                threads take a vertex there */
   int32_t local_chunks;      /* block-local push: most 1024-edge chunks of a unit one block may
                                 get before the push needs the global degree scan, 1 .. 2^20
-                                (default 4) */
+                                (default 4). No effect on graphs with no row above 32 entries,
+                                which never need the scan after a push */
 } dobfs_options;
 
 /* Fill *opt with the defaults (FULL, RATIO, alpha = beta = 0.01). */
@@ -220,13 +223,15 @@ typedef struct {
   float ms_total;           /* device time of the whole call (events) */
   float ms_init;            /* init kernel execution time (DOBFS_OPT_TIME_KERNELS) */
   int64_t reached;          /* vertices with depth >= 0 (multi-source: (vertex, source) pairs) */
-  /* Every launch of the per-level kernels in the call, counted the way a kernel profiler
-     counts them, with their summed execution times (DOBFS_OPT_TIME_KERNELS, else 0).
-     One step kernel, launched once per level, twice for a push level that needs the
-     global degree scan (every multi-source push level does), once more for the step that
-     finds the end, and for any steps enqueued past the end (they exit at once); when no
-     times are asked for, a launch may run several narrow push levels and counts as the
-     steps these would have taken; launches_aux and ms_aux_all are 0. The sort-based push mode leaves all four at 0. */
+  /* launches_main: the steps of the call's level loop, with their summed execution times
+     (DOBFS_OPT_TIME_KERNELS, else 0): one per level, two for a push level that needs the
+     global degree scan (every multi-source push level does), one for the step that finds
+     the end, and any enqueued past the end (they exit at once). A timed call launches the
+     step kernel once per step, so it is what a kernel profiler counts. In an untimed one a
+     launch may run several narrow push levels; it counts as the steps these take alone, so
+     there may have been fewer launches than this says. The persistent loop counts its
+     launches. launches_aux and ms_aux_all are 0. The sort-based push mode leaves all four
+     at 0. */
   int32_t launches_main;
   int32_t launches_aux;
   float ms_main_all;
@@ -279,15 +284,15 @@ dobfs_status dobfs_bfs(dobfs_graph g, int32_t source, const dobfs_options *opt, 
  * must not call hipMalloc: tight serving loops, harnesses that forbid it):
  * dobfs_bfs with the workspace and the level report in a static device array
  * of the library, DOBFS_STATIC_SCRATCH_BYTES and some control data on every
- * device the library runs this call on, held until the process ends. The call makes no allocation
- * (no hipMalloc / hipFree / hipHostMalloc, no events): it copies each batch's
- * report into ordinary host memory after the stream has drained, so it
- * synchronises `stream` once per batch of levels.
+ * device the library runs this call on, held until the process ends. The call
+ * makes no allocation (no hipMalloc / hipFree / hipHostMalloc, no events): it
+ * copies each batch's report into ordinary host memory after the stream has
+ * drained, so it synchronises `stream` once per batch of levels.
  * Results, arguments and errors as dobfs_bfs, and:
  *  - the graph must fit: 16*V + 4*ceil(V/32)*4 + 4*(nnz/1024) bytes plus
- *    about 200 KB of control data (256-byte aligned regions) within
- *    DOBFS_STATIC_SCRATCH_BYTES; V <= 2^22 with nnz <= 2^28 always fits (RMAT scale 22, edge
- *    factor 16). Larger graphs -> INVALID_ARG, nothing written;
+ *    about 200 KB (256-byte aligned regions) within
+ *    DOBFS_STATIC_SCRATCH_BYTES; V <= 2^22 with nnz <= 2^28 always fits (RMAT
+ *    scale 22, edge factor 16). Larger graphs -> INVALID_ARG, nothing written;
  *  - DOBFS_MODE_PUSH_SORT and DOBFS_OPT_TIME_KERNELS -> UNSUPPORTED (they
  *    need a larger workspace and events); stats receive no times (0);
  *  - every call on a device shares that device's array, which keeps the
@@ -346,8 +351,8 @@ dobfs_status dobfs_bfs_batch(dobfs_graph g, const int32_t *sources, int32_t k,
  * each on a host thread and HIP stream of its own, so queries that arrive
  * while a batch is on the GPU are admitted into the next free slot and run
  * beside it (continuous batching, not a single queue). Graphs whose batches
- * have taken more than 2 ms, or 256 levels, on average may occupy at most slots - 1 slots at
- * once, so a deep traversal never holds every slot, and their queries are
+ * have taken more than 2 ms, or 256 levels, on average may occupy at most
+ * slots - 1 slots at once, so a deep traversal never holds every slot, and their queries are
  * batched only once 8 of them are queued (fewer run one per slot). Admission by memory: the
  * server makes one device allocation of mem_budget bytes when it is created
  * and carves every batch's workspace out of it; a batch starts only when its

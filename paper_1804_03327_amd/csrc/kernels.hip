@@ -1169,7 +1169,8 @@ __device__ __forceinline__ void step_body(const BfsArgs& a, const LevelState& st
 // word an edge looks at before its claim may be stale; a stale word costs a claim that fails.
 //
 // Measured on 2048 x 2048 grids (2700 levels, frontiers up to 2758): 34.4 -> 11.6 ms per search
-// (12.5 -> 4.3 us per level); a tree of 750 000 vertices 505 -> 432 us. A burst level is bound by
+// (12.5 -> 4.3 us per level) with the search in one launch, 11.9 with 192 levels a batch
+// (run_steps); a tree of 750 000 vertices 505 -> 432 us. A burst level is bound by
 // its chain: neighbours, then visited words and row extents (0.8 us each when they miss the L2),
 // claims, totals. The limits (kBurstNf, kBurstEdges) are one round of a member's threads: a wider
 // level would take it two, and the whole chip runs levels of some ten thousand edges as fast.

@@ -12,8 +12,11 @@
 // Queries that arrive while a batch is on the GPU go to the next free slot,
 // so their traversal overlaps the running one on the device. Graphs whose
 // batches have been taking long (a running mean of their service times above
-// kLongMs, or of their level counts above kLongLevels) may hold at most slots - 1 slots at once, so one slot stays free for
-// the others' queries instead of queueing them behind deep traversals; and
+// kLongMs, or of their level counts above kLongLevels) may hold at most
+// slots - 1 slots at once, so one slot stays free for the others' queries
+// instead of queueing them behind deep traversals (whose launches are short:
+// the slots' streams share four hardware queues, and what one of them has
+// enqueued holds its queue for about a millisecond at most, see run_steps); and
 // their queries are batched only once kLongBatchMin of them are queued, fewer
 // going one per slot: on a deep graph a multi-source traversal of a few
 // sources takes longer than the same single-source traversals side by side.
@@ -38,12 +41,14 @@ namespace {
 
 constexpr int kMaxSlots = 16;
 constexpr double kLongMs = 2.0;  // a graph whose batches take longer than this on average is "long"
-// and so is one whose traversals are deeper than this on average: 0.6 to 1 ms of narrow levels or
+// and so is one whose traversals are deeper than this on average: a millisecond of narrow levels or
 // more, most of the chip idle, against about 0.1 ms for the shallow graphs a slot is kept free for
 constexpr double kLongLevels = 256.0;
-// Fewest queued queries of a long graph that one multi-source traversal takes (measured before
-// narrow levels shared launches; 2048x2048 grid: 2 / 4 / 8 sources took 84 / 100 / 99 ms together,
-// two single-source traversals on two streams 41 ms, one alone 32 ms, now 12 and 12 ms).
+// Fewest queued queries of a long graph that one multi-source traversal takes. 2 / 4 / 8 / 16 / 24
+// sources together against the same searches one by one on the three streams a long graph may have:
+// 2048 x 2048 grid 29 / 51 / 78 / 103 / 113 ms against 13 / 24 / 41 / 85 / 124, 4000 x 60 grid
+// 19 / 28 / 28 / 29 / 30 against 9 / 19 / 26 / 54 / 82, 400 x 400 grid 5 / 5 / 6 / 7 / 12 against
+// 3 / 5 / 8 / 16 / 23: even at 19, 8 and 4.
 constexpr int32_t kLongBatchMin = 8;
 
 // First-fit allocator over one device allocation, in 256-byte units.
